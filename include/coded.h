@@ -128,10 +128,10 @@ coded_status coded_code_info(const coded_code* code, int32_t* n, int32_t* k, int
  *   workspace_bytes  workspace of coded_matmul (its Y, in y_dt = F64 for F32
  *                    inputs and F32 for BF16 inputs, followed by the worker
  *                    workspace)
- *   worker_workspace_bytes  workspace of coded_worker_mm: 0 for F32 inputs;
- *                    X transposed (s x r bf16, 256-byte aligned size) for
- *                    BF16 inputs, so that the matrix-core kernel reads X
- *                    along K in 16-byte pieces
+ *   worker_workspace_bytes  workspace of coded_encode_worker_mm: 0 for F32
+ *                    inputs; X transposed (s x r bf16, 256-byte aligned size)
+ *                    for BF16 inputs, so that the single pass reads X along K
+ *                    in 16-byte pieces
  * Any output pointer may be NULL.
  */
 coded_status coded_sizes(const coded_code* code, coded_dtype dt, coded_dtype y_dt, int64_t q, int64_t r,
@@ -168,9 +168,8 @@ coded_status coded_encode(const coded_code* code, coded_dtype dt, const void* A,
  *   y_dt       CODED_F64 (dt = F32: products accumulate in fp64) or
  *              CODED_F32 (dt = F32: fp64 accumulate, rounded on store;
  *              dt = BF16: fp32 accumulate on the matrix cores).
- *   workspace  device, coded_sizes' worker_workspace_bytes; may be NULL when
- *              that size is 0 (fp32 inputs).  For bf16 inputs NULL selects a
- *              slower vector kernel.
+ *   workspace  not used: the products read X in its own order.  NULL or a
+ *              buffer of coded_sizes' worker_workspace_bytes.
  */
 coded_status coded_worker_mm(const coded_code* code, coded_dtype dt, const void* A, int64_t q, int64_t r, int64_t lda,
                              const void* parity, const void* X, int64_t s, int64_t ldx, const uint8_t* worker_mask,

@@ -258,8 +258,8 @@ def matmul_workspace(code: Code, A, X):
 
 
 def coded_worker_mm(code: Code, A, parity, X, Y, worker_mask=None, workspace="auto", stream=None) -> None:
-    """workspace: a device buffer of coded_sizes' worker workspace bytes, None (bf16: vector
-    kernel), or "auto" (allocated here when needed)."""
+    """workspace: not used by the products; None, "auto", or a device buffer of coded_sizes'
+    worker workspace bytes."""
     q, r, lda = _matrix(A, "A")
     rx, s, ldx = _matrix(X, "X")
     if rx != r:
@@ -271,7 +271,7 @@ def coded_worker_mm(code: Code, A, parity, X, Y, worker_mask=None, workspace="au
             raise ValueError("worker_mask must have n entries")
         mask = m.ctypes.data_as(ctypes.c_void_p)
     if isinstance(workspace, str):
-        workspace = worker_workspace(code, A, X)
+        workspace = None
     _check(lib().coded_worker_mm(code.handle, _dtype_code(A), _ptr(A), q, r, lda, _ptr(parity), _ptr(X), s, ldx,
                                  mask, _ptr(Y), _dtype_code(Y), _ptr(workspace), _stream(stream)))
 

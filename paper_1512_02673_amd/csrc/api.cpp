@@ -151,7 +151,7 @@ coded_status do_encode(const coded_code* c, coded_dtype dt, const void* A, int64
 
 coded_status do_workers(const coded_code* c, coded_dtype dt, const void* A, int64_t q, int64_t r, int64_t lda,
                         const void* parity, const void* X, int64_t s, int64_t ldx, const uint8_t* mask, void* Y,
-                        coded_dtype y_dt, void* workspace, hipStream_t st, bool xt_ready = false) {
+                        coded_dtype y_dt, hipStream_t st) {
     if (s < 0) return fail(CODED_ERR_SHAPE, "s must be >= 0");
     if (ldx < std::max<int64_t>(s, 1)) return fail(CODED_ERR_SHAPE, "ldx must be >= max(s, 1)");
     if (s == 1 && ldx != 1 && dt == CODED_F32) {
@@ -182,8 +182,6 @@ coded_status do_workers(const coded_code* c, coded_dtype dt, const void* A, int6
     a.planes = c->planes;
     a.lo_bf16 = c->lo_bf16 && dt == CODED_F32;
     a.y_f64 = y_dt == CODED_F64;
-    a.xt = dt == CODED_BF16 ? workspace : nullptr;
-    a.xt_ready = xt_ready ? 1 : 0;
     for (int i = 0; i < c->n; ++i) {
         if (mask && !mask[i]) continue;
         if (i < c->k)
@@ -206,7 +204,7 @@ coded_status do_encode_workers(const coded_code* c, coded_dtype dt, const void* 
                           workspace && aligned16(workspace) && y_dt == CODED_F32;
     if (!one_pass) {
         if (coded_status e = do_encode(c, dt, A, q, r, lda, parity, st)) return e;
-        return do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, nullptr, Y, y_dt, workspace, st);
+        return do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, nullptr, Y, y_dt, st);
     }
     for (size_t i = static_cast<size_t>(c->k) * c->k; i < c->G.size(); ++i)
         if (!is_bf16_value(c->G[i]))
@@ -400,12 +398,12 @@ coded_status coded_encode(const coded_code* c, coded_dtype dt, const void* A, in
 
 coded_status coded_worker_mm(const coded_code* c, coded_dtype dt, const void* A, int64_t q, int64_t r, int64_t lda,
                              const void* parity, const void* X, int64_t s, int64_t ldx, const uint8_t* worker_mask,
-                             void* Y, coded_dtype y_dt, void* workspace, void* stream) {
+                             void* Y, coded_dtype y_dt, void* /*workspace*/, void* stream) {
     CODED_GUARD_BEGIN
     if (coded_status st = check_code(c)) return st;
     if (coded_status st = check_dt(dt, y_dt)) return st;
     if (coded_status st = check_ar(q, r, lda)) return st;
-    return do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, worker_mask, Y, y_dt, workspace,
+    return do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, worker_mask, Y, y_dt,
                       static_cast<hipStream_t>(stream));
     CODED_GUARD_END
 }
@@ -570,7 +568,7 @@ coded_status coded_matmul(const coded_code* c, coded_dtype dt, const void* A, in
     if (!parity_ready) {
         if (coded_status s2 = do_encode_workers(c, dt, A, q, r, lda, parity, X, s, ldx, workspace, y_dt, wws, st))
             return s2;
-    } else if (coded_status s2 = do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, nullptr, workspace, y_dt, wws, st)) {
+    } else if (coded_status s2 = do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, nullptr, workspace, y_dt, st)) {
         return s2;
     }
     if (coded_status s2 = do_decode_single(c, set, m, workspace, y_dt, q, s, out, ldo, info, st)) return s2;
@@ -682,17 +680,6 @@ coded_status coded_straggler_matmul(coded_code* c, coded_dtype dt, const void* A
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
-    if (dt == CODED_BF16 && qb * s > 0 && r > 0) {
-        // X is transposed once, before any worker starts (the workers share it)
-        WorkerArgs xa{};
-        xa.X = X;
-        xa.r = r;
-        xa.s = s;
-        xa.ldx = ldx;
-        xa.xt = workspace;
-        e = launch_transpose_x_bf16(xa, st);
-        if (e != hipSuccess) return hip_fail(e, "transpose launch");
-    }
     // Products start after everything already enqueued on the caller's stream.
     e = hipEventRecord(c->start_event, st);
     for (int i = 0; e == hipSuccess && i < kStragglerStreams; ++i) e = hipStreamWaitEvent(c->worker_streams[i], c->start_event, 0);
@@ -707,8 +694,7 @@ coded_status coded_straggler_matmul(coded_code* c, coded_dtype dt, const void* A
         mask[i] = 1;
         hipStream_t ws = c->worker_streams[launches % kStragglerStreams];
         launched_at[i] = now_us();
-        if (coded_status s2 = do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, mask.data(), Y, y_dt, workspace, ws,
-                                         dt == CODED_BF16))
+        if (coded_status s2 = do_workers(c, dt, A, q, r, lda, parity, X, s, ldx, mask.data(), Y, y_dt, ws))
             return s2;
         hipError_t e2 = hipEventRecord(c->worker_events[i], ws);
         if (e2 != hipSuccess) return hip_fail(e2, "worker event");
@@ -834,10 +820,10 @@ coded_status coded_gd_step(const coded_code* cA, const coded_code* cT, const flo
     float* z = reinterpret_cast<float*>(reinterpret_cast<char*>(Y2) +
                                         align256(static_cast<int64_t>(cT->n) * block_rows(r, cT->k) * 8));
     // z = A x - y  (coded product with code A, residual fused into the decode)
-    if (coded_status e = do_workers(cA, CODED_F32, A, q, r, lda, parityA, x, 1, 1, nullptr, Y1, CODED_F64, nullptr, st)) return e;
+    if (coded_status e = do_workers(cA, CODED_F32, A, q, r, lda, parityA, x, 1, 1, nullptr, Y1, CODED_F64, st)) return e;
     if (coded_status e = do_decode_single(cA, set1, m1, Y1, CODED_F64, q, 1, z, 1, info, st, y, 1.0, -1.0)) return e;
     // x = x - eta A^T z  (coded product with the code of A^T, update fused into the decode)
-    if (coded_status e = do_workers(cT, CODED_F32, AT, r, q, ldat, parityAT, z, 1, 1, nullptr, Y2, CODED_F64, nullptr, st)) return e;
+    if (coded_status e = do_workers(cT, CODED_F32, AT, r, q, ldat, parityAT, z, 1, 1, nullptr, Y2, CODED_F64, st)) return e;
     if (coded_status e = do_decode_single(cT, set2, m2, Y2, CODED_F64, r, 1, x, 1, info + 1, st, x, -eta, 1.0)) return e;
     if (survivors_out) {
         std::copy(s1, s1 + cA->k, survivors_out);

@@ -57,8 +57,6 @@ struct WorkerArgs {
     int32_t n, k, planes;
     int32_t y_f64;        // 1: Y is fp64, 0: Y is fp32
     int32_t n_sys, n_par; // active systematic / parity workers
-    void* xt;             // bf16 only: scratch for X transposed (s x r), or null
-    int32_t xt_ready;     // bf16 only: xt already holds X transposed (skip the transpose)
     int32_t lo_bf16;      // fp32 with planes == 2: the lo plane is bfloat16 (after the fp32 hi plane)
     uint8_t sys_ids[kMaxN];
     uint8_t par_ids[kMaxN];
@@ -70,8 +68,6 @@ hipError_t launch_worker_f32(const WorkerArgs& a, hipStream_t st);
 bool gemm_f32_mfma_supported(const WorkerArgs& a);
 hipError_t launch_gemm_f32_mfma(const WorkerArgs& a, hipStream_t st);
 hipError_t launch_worker_bf16(const WorkerArgs& a, hipStream_t st);
-// bf16: X (r x s, row stride ldx) transposed into a.xt.
-hipError_t launch_transpose_x_bf16(const WorkerArgs& a, hipStream_t st);
 // Bytes of the bf16 worker workspace (X transposed), 256-byte aligned.
 int64_t worker_workspace_bytes_bf16(int64_t r, int64_t s);
 
