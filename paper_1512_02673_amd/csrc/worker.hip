@@ -7,12 +7,17 @@
 // buffer; its product is sum_h plane_h X.
 //
 // The single-vector case (s == 1) is the HBM-bound GEMV: every byte of A and
-// of the parity planes is read exactly once, in 16-byte non-temporal loads
-// that a whole workgroup issues over one contiguous stretch of a row at a time
-// (streaming each row through a single wavefront instead measurably loses
-// bandwidth).  Products of two fp32 values are exact in fp64 and are summed
-// in fp64.  s > 1 runs on the fp64 matrix cores (worker_f32_mfma.hip);
-// unaligned shapes take a general vector kernel.
+// of the parity planes is read exactly once, in 16-byte loads that a whole
+// workgroup issues over one contiguous stretch of a long row at a time
+// (streaming long rows through single wavefronts measurably loses bandwidth);
+// short rows go to 16 or 64 lanes each.  Rows start at any fp32 boundary and
+// have any length ((25,23) on 11500 x 5750: 52 us, 6.0 TB/s; scalar loads took
+// 154).  Products of two fp32 values are exact in fp64 and are summed in fp64.
+// s > 1 runs on the fp64 matrix cores (worker_f32_mfma.hip); what that cannot
+// take runs a general vector kernel.
+#include <algorithm>
+#include <type_traits>
+
 #include "internal.h"
 #include "worker_common.h"
 
@@ -21,27 +26,26 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// 16-byte streaming load: the data is used once, so it is marked non-temporal
-// to keep it from displacing X in the caches.
-__device__ inline float4 load_stream(const float* p) {
+// Four values from any fp32 boundary: 16-byte loads at a 4-byte boundary run
+// at 6.7-6.9 TB/s against 7.1 aligned (scalar loads of the same rows: 5.5).
+// NTL: non-temporal, for data that no later call finds in a cache.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+template <bool NTL>
+__device__ inline float4 load4(const float* p) {
     // a global-memory pointer, so the load is a global (not flat) load
-    typedef const __attribute__((address_space(1))) f32x4* gptr;
-    const f32x4 v = __builtin_nontemporal_load((gptr)(p));
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ inline float4 load_global4(const float* p) {
-    typedef const __attribute__((address_space(1))) f32x4* gptr;
-    const f32x4 v = *(gptr)(p);
+    typedef const __attribute__((address_space(1))) f32x4_any* gptr;
+    const f32x4 v = NTL ? __builtin_nontemporal_load((gptr)(p)) : *(gptr)(p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// Four bfloat16 values (8 bytes, streamed) as raw bits, and their exact
-// widening to fp32 (kept apart so a select can take the raw load).
+// Four bfloat16 values (8 bytes, any bf16 boundary) as raw bits, and their
+// exact widening to fp32 (kept apart so a select can take the raw load).
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-__device__ inline u32x2 load_stream_bf16x4(const uint16_t* p) {
-    // a global-memory pointer, so the load is a global (not flat) load
-    typedef const __attribute__((address_space(1))) u32x2* gptr;
-    return __builtin_nontemporal_load((gptr)(p));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+template <bool NTL>
+__device__ inline u32x2 load_bf16x4(const uint16_t* p) {
+    typedef const __attribute__((address_space(1))) u32x2_any* gptr;
+    return NTL ? __builtin_nontemporal_load((gptr)(p)) : *(gptr)(p);
 }
 __device__ inline float4 widen_bf16x4(u32x2 v) {
     return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u),
@@ -96,7 +100,8 @@ __device__ inline RowRef plane_row(const WorkerArgs& a, int w, int64_t pr, bool 
 // are combined across lanes (shuffles) and waves (LDS) in a fixed order.
 // LO16: the lo plane is bfloat16 (8-byte loads of four values, widened
 // exactly to fp32, so the products stay exact in fp64).
-template <int T, int XR, int NT, bool LO16>
+// TAIL: r is no multiple of 4; the last r % 4 elements go to the first threads.
+template <int T, int XR, int NT, bool LO16, bool NTL, bool TAIL>
 __global__ __launch_bounds__(NT) void gemv_wg_kernel(WorkerArgs a) {
     constexpr int NW = NT / 64;
     constexpr int kChunk = NT * 4 * XR;
@@ -169,12 +174,13 @@ __global__ __launch_bounds__(NT) void gemv_wg_kernel(WorkerArgs a) {
 #pragma unroll
     for (int i = 0; i < T; ++i) acc[i] = 0.0;
 
-    for (int64_t cb = 0; cb < r; cb += kChunk) {
+    const int64_t r4 = TAIL ? r & ~int64_t{3} : r;
+    for (int64_t cb = 0; cb < r4; cb += kChunk) {
         float4 xv[XR];
 #pragma unroll
         for (int j = 0; j < XR; ++j) {
             const int64_t c = cb + tid * 4 + j * NT * 4;
-            xv[j] = c < r ? load_global4(x + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+            xv[j] = c < r4 ? load4<false>(x + c) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
         for (int i = 0; i < T; ++i) {
@@ -191,7 +197,7 @@ __global__ __launch_bounds__(NT) void gemv_wg_kernel(WorkerArgs a) {
                     if constexpr (LO16) {
                         if (h == 1) continue;
                     }
-                    av[j] = c < r ? load_stream(row + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    av[j] = c < r4 ? load4<NTL>(row + c) : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
                 if constexpr (LO16) {
                     if (h == 1) {
@@ -199,7 +205,7 @@ __global__ __launch_bounds__(NT) void gemv_wg_kernel(WorkerArgs a) {
 #pragma unroll
                         for (int j = 0; j < XR; ++j) {
                             const int64_t c = cb + tid * 4 + j * NT * 4;
-                            raw[j] = c < r ? load_stream_bf16x4(lo16[i] + c) : u32x2{0u, 0u};
+                            raw[j] = c < r4 ? load_bf16x4<NTL>(lo16[i] + c) : u32x2{0u, 0u};
                         }
 #pragma unroll
                         for (int j = 0; j < XR; ++j) av[j] = widen_bf16x4(raw[j]);
@@ -215,6 +221,17 @@ __global__ __launch_bounds__(NT) void gemv_wg_kernel(WorkerArgs a) {
             }
         }
     }
+    if constexpr (TAIL) {
+        if (tid < static_cast<int>(r - r4)) {
+            const double xt = x[r4 + tid];
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                if (rows[i][0]) acc[i] = fma(static_cast<double>(rows[i][0][r4 + tid]), xt, acc[i]);
+                if (rows[i][1]) acc[i] = fma(static_cast<double>(rows[i][1][r4 + tid]), xt, acc[i]);
+                if (LO16 && lo16[i]) acc[i] = fma(static_cast<double>(bf16_bits_to_f32(lo16[i][r4 + tid])), xt, acc[i]);
+            }
+        }
+    }
 #pragma unroll
     for (int i = 0; i < T; ++i) {
         const double v = wave_sum(acc[i]);
@@ -227,6 +244,134 @@ __global__ __launch_bounds__(NT) void gemv_wg_kernel(WorkerArgs a) {
         for (int w = 0; w < NW; ++w) v += red[w][tid];
         const int64_t t = t0 + tid;
         if (t < a.qb) store_y(a, worker, t, 0, v);
+    }
+}
+
+// s == 1, short rows (r <= 16 * LPR): LPR lanes (16 or 64) per row, so a row
+// of a few hundred elements does not leave most of a workgroup idle (r = 400:
+// 100 of 256 threads in the kernel above; a (10,8) code on 10000 x 400 13.6 us
+// there, 5.7 here; 60000 x 256 50 and 16.5 us, 5.6 TB/s), and the sum of a row
+// stays inside a wave.  A group of LPR lanes owns T consecutive rows of one worker's block,
+// all their loads in flight at once; its slice of x (XR pieces of four, XR * 4
+// * LPR >= r) stays in registers.  Rows past the block, or past A, read the
+// last row and are not stored, or stored as the zero padding, so there is no
+// branch between the loads.
+template <int T, int XR, int LPR, bool LO16, bool NTL, bool TAIL>
+__global__ __launch_bounds__(256) void gemv_short_kernel(WorkerArgs a) {
+    constexpr int kGroups = 256 / LPR, kTile = kGroups * T;
+    const int tid = threadIdx.x;
+    const int l = tid % LPR;
+    const int gi = LPR == 64 ? __builtin_amdgcn_readfirstlane(tid / LPR) : tid / LPR;
+    const float* Ap = static_cast<const float*>(a.A);
+    const float* Pp = static_cast<const float*>(a.parity);
+    const float* x = static_cast<const float*>(a.X);
+    int64_t q = a.q, lda = a.lda, qb = a.qb;
+    int32_t r = static_cast<int32_t>(a.r), n = a.n, k = a.k, planes = a.planes, n_sys = a.n_sys, n_par = a.n_par;
+    // one batch of scalar loads, as above
+    asm volatile("" : "+s"(Ap), "+s"(Pp), "+s"(x), "+s"(q), "+s"(r), "+s"(lda), "+s"(qb), "+s"(n), "+s"(k),
+                 "+s"(planes), "+s"(n_sys), "+s"(n_par));
+    // parity workgroups (twice the bytes) first
+    const uint32_t groups = static_cast<uint32_t>(ceil_div(qb, kTile));
+    const uint32_t npar = groups * static_cast<uint32_t>(n_par);
+    const uint32_t g = blockIdx.x;
+    const bool parity = g < npar;
+    const uint32_t g2 = parity ? g : g - npar;
+    const uint32_t wi = g2 / groups;
+    if (!parity && wi >= static_cast<uint32_t>(n_sys)) return;
+    int worker;
+    if (parity)
+        worker = n_par == n - k ? k + static_cast<int>(wi) : a.par_ids[wi];
+    else
+        worker = n_sys == k ? static_cast<int>(wi) : a.sys_ids[wi];
+    const int64_t t0 = static_cast<int64_t>(g2 - wi * groups) * kTile + gi * T;
+    const int64_t plane = static_cast<int64_t>(n - k) * qb * r;
+
+    const float* row[T];
+    int64_t off[T];            // parity: element offset of the row in a plane
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        const int64_t t = min(t0 + i, qb - 1);
+        off[i] = parity ? (static_cast<int64_t>(worker - k) * qb + t) * r : 0;
+        row[i] = parity ? Pp + off[i] : Ap + min(static_cast<int64_t>(worker) * qb + t, q - 1) * lda;
+    }
+    const int r4 = TAIL ? r & ~3 : r;
+    const int rem = r - r4;
+    float4 xv[XR];
+    float xt = 0.f;
+#pragma unroll
+    for (int j = 0; j < XR; ++j) {
+        const int c = (l + j * LPR) * 4;
+        xv[j] = c < r4 ? load4<false>(x + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (TAIL && l < rem) xt = x[r4 + l];
+
+    double acc[T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) acc[i] = 0.0;
+    auto add = [&](const float4 (&v)[T][XR], const float (&vt)[T]) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+#pragma unroll
+            for (int j = 0; j < XR; ++j) {
+                acc[i] = fma(static_cast<double>(v[i][j].x), static_cast<double>(xv[j].x), acc[i]);
+                acc[i] = fma(static_cast<double>(v[i][j].y), static_cast<double>(xv[j].y), acc[i]);
+                acc[i] = fma(static_cast<double>(v[i][j].z), static_cast<double>(xv[j].z), acc[i]);
+                acc[i] = fma(static_cast<double>(v[i][j].w), static_cast<double>(xv[j].w), acc[i]);
+            }
+            if (TAIL) acc[i] = fma(static_cast<double>(vt[i]), static_cast<double>(xt), acc[i]);
+        }
+    };
+    auto sweep = [&](int64_t shift) {
+        float4 v[T][XR];
+        float vt[T];
+#pragma unroll
+        for (int j = 0; j < XR; ++j) {
+            const int c = (l + j * LPR) * 4;
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+                v[i][j] = c < r4 ? load4<NTL>(row[i] + shift + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int i = 0; i < T; ++i) vt[i] = TAIL && l < rem ? row[i][shift + r4 + l] : 0.f;
+        add(v, vt);
+    };
+    sweep(0);
+    if (parity && planes == 2) {
+        if constexpr (LO16) {
+            const uint16_t* lo = reinterpret_cast<const uint16_t*>(Pp + plane);
+            u32x2 raw[T][XR];
+            float4 v[T][XR];
+            float vt[T];
+#pragma unroll
+            for (int j = 0; j < XR; ++j) {
+                const int c = (l + j * LPR) * 4;
+#pragma unroll
+                for (int i = 0; i < T; ++i) raw[i][j] = c < r4 ? load_bf16x4<NTL>(lo + off[i] + c) : u32x2{0u, 0u};
+            }
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                vt[i] = TAIL && l < rem ? bf16_bits_to_f32(lo[off[i] + r4 + l]) : 0.f;
+#pragma unroll
+                for (int j = 0; j < XR; ++j) v[i][j] = widen_bf16x4(raw[i][j]);
+            }
+            add(v, vt);
+        } else {
+            sweep(plane);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+#pragma unroll
+        for (int o = LPR / 2; o >= 1; o >>= 1) acc[i] += __shfl_xor(acc[i], o, 64);
+    }
+    if (l == 0) {
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int64_t t = t0 + i;
+            if (t >= qb) break;
+            const bool inside = parity || static_cast<int64_t>(worker) * qb + t < q;
+            store_y(a, worker, t, 0, inside ? acc[i] : 0.0);
+        }
     }
 }
 
@@ -268,8 +413,6 @@ __global__ __launch_bounds__(kThreads) void gemm_small_f32_kernel(WorkerArgs a) 
     }
 }
 
-bool aligned(const void* p, int bytes) { return (reinterpret_cast<uintptr_t>(p) % bytes) == 0; }
-
 template <typename K>
 hipError_t launch_waves(K kernel, const WorkerArgs& a, int64_t wsys, int64_t wpar, hipStream_t st) {
     const int64_t waves = wsys * a.n_sys + wpar * a.n_par;
@@ -282,44 +425,88 @@ hipError_t launch_waves(K kernel, const WorkerArgs& a, int64_t wsys, int64_t wpa
 
 }  // namespace
 
-template <int T, int XR>
-hipError_t launch_gemv_wg(const WorkerArgs& a, hipStream_t st) {
+// What a launch of products reads from A and the parity planes.
+static int64_t read_bytes(const WorkerArgs& a) {
+    const int64_t par = static_cast<int64_t>(a.n_par) * a.qb * a.r;
+    const int64_t planes = a.planes == 1 ? 4 : (a.lo_bf16 ? 6 : 8);
+    return 4 * a.r * std::min(a.q, a.n_sys * a.qb) + planes * par;
+}
+
+template <int T, int XR, bool LO16, bool NTL, bool TAIL>
+static hipError_t launch_gemv_v(const WorkerArgs& a, hipStream_t st) {
     const int64_t blocks = ceil_div(a.qb, T) * (a.n_sys + a.n_par);
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-    // Rows of 8 column slots per thread: at most three workgroups per compute
-    // unit (each requests 40 KB of the 160 KB of LDS, which it does not use),
-    // which streams these long rows best (measured: two, three and four).
-    const size_t cap = XR >= 8 ? 40 * 1024 : 0;
-    if (a.lo_bf16 && a.planes == 2)
-        hipLaunchKernelGGL((gemv_wg_kernel<T, XR, 256, true>), dim3(static_cast<unsigned>(blocks)), dim3(256), cap,
-                           st, a);
-    else
-        hipLaunchKernelGGL((gemv_wg_kernel<T, XR, 256, false>), dim3(static_cast<unsigned>(blocks)), dim3(256), cap,
-                           st, a);
+    // Rows of 8 column slots per thread that stream from HBM: at most three
+    // workgroups per compute unit (each requests 40 KB of the 160 KB of LDS,
+    // which it does not use), which streams these long rows best (measured:
+    // two, three and four; 65536 x 8192: 521.8 us against 524.1 without).
+    // From the memory-side cache the limit costs (1472 x 7307: 12.5 us
+    // against 10.7).
+    const size_t cap = XR >= 8 && NTL ? 40 * 1024 : 0;
+    hipLaunchKernelGGL((gemv_wg_kernel<T, XR, 256, LO16, NTL, TAIL>), dim3(static_cast<unsigned>(blocks)), dim3(256),
+                       cap, st, a);
     return hipGetLastError();
 }
 
-template <int XR>
-hipError_t launch_gemv_t(const WorkerArgs& a, hipStream_t st) {
-    // Four rows per workgroup (x is read once per four rows) unless that
-    // leaves fewer than four workgroups per compute unit (256 CUs); then fewer.
+template <int T, int XR, int LPR, bool LO16, bool NTL, bool TAIL>
+static hipError_t launch_short_v(const WorkerArgs& a, hipStream_t st) {
+    const int64_t blocks = ceil_div(a.qb, 256 / LPR * T) * (a.n_sys + a.n_par);
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((gemv_short_kernel<T, XR, LPR, LO16, NTL, TAIL>), dim3(static_cast<unsigned>(blocks)), dim3(256),
+                       0, st, a);
+    return hipGetLastError();
+}
+
+// The plane format, the tail and the cache policy as template arguments.
+// Plain loads while everything read fits the 256 MB memory-side cache, where
+// the next call finds it; non-temporal loads above (65536 x 8192: 522 us
+// against 587 with plain loads).
+template <int T, int XR, int LPR>
+static hipError_t launch_gemv_any(const WorkerArgs& a, hipStream_t st) {
+    const bool lo16 = a.lo_bf16 && a.planes == 2, tail = a.r % 4 != 0;
+    const bool ntl = read_bytes(a) > (256ll << 20);
+    auto go = [&](auto lo, auto nt, auto tl) {
+        constexpr bool L = decltype(lo)::value, N = decltype(nt)::value, TL = decltype(tl)::value;
+        if constexpr (LPR == 256)
+            return launch_gemv_v<T, XR, L, N, TL>(a, st);
+        else
+            return launch_short_v<T, XR, LPR, L, N, TL>(a, st);
+    };
+    auto go2 = [&](auto lo, auto nt) { return tail ? go(lo, nt, std::true_type{}) : go(lo, nt, std::false_type{}); };
+    auto go3 = [&](auto lo) { return ntl ? go2(lo, std::true_type{}) : go2(lo, std::false_type{}); };
+    return lo16 ? go3(std::true_type{}) : go3(std::false_type{});
+}
+
+template <int XR, int LPR>
+static hipError_t launch_gemv_t(const WorkerArgs& a, hipStream_t st) {
+    // Four rows per workgroup, or group of lanes (x is read once per four
+    // rows), unless that leaves fewer than four workgroups per compute unit
+    // (256 CUs); then fewer.
     const int64_t workers = a.n_sys + a.n_par;
-    if (ceil_div(a.qb, 4) * workers >= 1024) return launch_gemv_wg<4, XR>(a, st);
-    if (ceil_div(a.qb, 2) * workers >= 1024) return launch_gemv_wg<2, XR>(a, st);
-    return launch_gemv_wg<1, XR>(a, st);
+    constexpr int G = 256 / LPR;
+    if (ceil_div(a.qb, 4 * G) * workers >= 1024) return launch_gemv_any<4, XR, LPR>(a, st);
+    if (ceil_div(a.qb, 2 * G) * workers >= 1024) return launch_gemv_any<2, XR, LPR>(a, st);
+    return launch_gemv_any<1, XR, LPR>(a, st);
 }
 
 hipError_t launch_worker_f32(const WorkerArgs& a, hipStream_t st) {
     if (a.qb == 0) return hipSuccess;
-    const bool vec = a.s == 1 && a.ldx == 1 && (a.r % 4 == 0) && (a.lda % 4 == 0) && aligned(a.A, 16) &&
-                     aligned(a.X, 16) && (a.parity == nullptr || aligned(a.parity, 16));
-    if (vec) {
-        // Column slots per thread: the whole row in registers up to 8192 columns.
-        if (a.r > 4096) return launch_gemv_t<8>(a, st);
-        if (a.r > 2048) return launch_gemv_t<4>(a, st);
-        if (a.r > 1024) return launch_gemv_t<2>(a, st);
-        return launch_gemv_t<1>(a, st);
+    if (a.s == 1 && a.ldx == 1) {
+        // Column slots per thread: the whole row in registers up to 8192
+        // columns.  Rows of up to 1024 are short: a row per 16 or 64 lanes.
+        // Six slots up to 6144 (eight leave a third of them idle: 11500 x
+        // 5750 52 us against 62, 20000 x 4097 92 against 102).
+        if (a.r > 6144) return launch_gemv_t<8, 256>(a, st);
+        if (a.r > 4096) return launch_gemv_t<6, 256>(a, st);
+        if (a.r > 2048) return launch_gemv_t<4, 256>(a, st);
+        if (a.r > 1024) return launch_gemv_t<2, 256>(a, st);
+        if (a.r > 512) return launch_gemv_t<4, 64>(a, st);
+        if (a.r > 256) return launch_gemv_t<2, 64>(a, st);
+        if (a.r > 128) return launch_gemv_t<4, 16>(a, st);
+        if (a.r > 64) return launch_gemv_t<2, 16>(a, st);
+        return launch_gemv_t<1, 16>(a, st);
     }
     if (gemm_f32_mfma_supported(a)) return launch_gemm_f32_mfma(a, st);
     return launch_waves(gemm_small_f32_kernel<4>, a, a.qb, a.qb, st);
