@@ -228,7 +228,7 @@ coded_status take_survivors(const coded_code* c, const int32_t* survivors, int32
     std::memset(&set, 0, sizeof(set));
     m = 0;
     for (int i = 0; i < c->k; ++i) {
-        set.packed[i / 4] |= static_cast<uint32_t>(v[i]) << (8 * (i % 4));
+        set.mask[v[i] / 64] |= uint64_t{1} << (v[i] % 64);
         m += v[i] >= c->k;
     }
     return CODED_OK;

@@ -165,11 +165,11 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a, DecodeSe
                     }
                 }
                 if (best == 0.0) sm.status = first_par + j + 1;
-                sm.raw[0] = p;                     // reuse: pivot row of this step
+                sm.pivot = p;
             }
             __syncthreads();
             if (sm.status != 0) break;
-            const int p = sm.raw[0];
+            const int p = sm.pivot;
             if (p != j) {
                 for (int c = tid; c < m; c += kThreads) {
                     const double t0 = sMat[j * ST + c];
@@ -450,30 +450,71 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
         }
     }
 
-    // E == 4: the copying wave takes the systematic survivors block by block,
-    // U four-element items per lane in flight (a batch past the block's end
-    // re-reads its last item and stores nothing).  With dense output rows
-    // (ldo == s) element e of a block is at offset e from its first row.
+    // E == 4: the copying wave takes the systematic survivors.  Long chunks go
+    // block by block, U four-element items per lane in flight (a batch past
+    // the block's end re-reads its last item and stores nothing), the block's
+    // addresses in scalar registers.  Chunks of up to 128 such items go as one
+    // sequence of (block, four elements) items: block by block, a chunk of 64
+    // elements leaves three quarters of the lanes idle and waits for memory
+    // once per block ((25,23), 16 columns: 13.2 us against 5.7).  With dense
+    // output rows (ldo == s) element e of a block is at offset e from its
+    // first row.
     if constexpr (E == 4) {
         if (wv == ew) {
-            constexpr int U = 4;
+            constexpr int U = sizeof(YT) == 8 ? 4 : 8;
             const bool dense = a.ldo == a.s;
-            for (int c = 0; c < first_par; ++c) {
-                const int w = sm.S[c];
-                const YT* yr = Y + sm.yoff[c];
-                float* ob = out + sm.ooff[w];
-                const int elim = min(e1, sm.lim[w] * s);    // the block's elements inside A
-                for (int e = e0 + 4 * lane; e < elim; e += 256 * U) {
-                    float v[U][4];
+            const uint32_t nq = static_cast<uint32_t>(e1 - e0) / 4;
+            const uint32_t citems = nq * static_cast<uint32_t>(first_par);   // nq k < 2^31 / 4
+            if (nq == 0) return;
+            if (nq > 128) {
+                for (int c = 0; c < first_par; ++c) {
+                    const int w = __builtin_amdgcn_readfirstlane(sm.S[c]);
+                    const YT* yr = Y + static_cast<int64_t>(w) * total;
+                    float* ob = out + static_cast<int64_t>(w) * a.qb * a.ldo;
+                    const int elim = min(e1, __builtin_amdgcn_readfirstlane(sm.lim[w]) * s);   // inside A
+                    for (int e = e0 + 4 * lane; e < elim; e += 1024) {
+                        float v[4][4];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) load_f32<4, YT>(yr + min(e + 256 * u, elim - 4), v[u]);
+                        for (int u = 0; u < 4; ++u) load_f32<4, YT>(yr + min(e + 256 * u, elim - 4), v[u]);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int ee = e + 256 * u;
-                        if (ee < elim) {
-                            const int64_t off = dense ? ee : static_cast<int64_t>(ee / s) * a.ldo + ee % s;
-                            store_out<4>(a, ob, off, v[u]);
+                        for (int u = 0; u < 4; ++u) {
+                            const int ee = e + 256 * u;
+                            if (ee < elim) {
+                                const int64_t off = dense ? ee : static_cast<int64_t>(ee / s) * a.ldo + ee % s;
+                                store_out<4>(a, ob, off, v[u]);
+                            }
                         }
+                    }
+                }
+                return;
+            }
+            const uint32_t dc = 64 / nq, de = 64 % nq;
+            uint32_t c = static_cast<uint32_t>(lane) / nq, eq = static_cast<uint32_t>(lane) % nq;
+            for (uint32_t it = lane; it < citems; it += 64 * U) {
+                float v[U][4];
+                int32_t we[U];         // block of item u, -1 for none, and its element
+                int ee[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool live = it + 64 * u < citems;
+                    const uint32_t cc = live ? c : 0;
+                    const int w = sm.S[cc];
+                    const int e = e0 + 4 * static_cast<int>(live ? eq : 0);
+                    load_f32<4, YT>(Y + sm.yoff[cc] + e, v[u]);
+                    ee[u] = e;
+                    we[u] = live && e < sm.lim[w] * s ? w : -1;
+                    c += dc;
+                    eq += de;
+                    if (eq >= nq) {
+                        eq -= nq;
+                        ++c;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (we[u] >= 0) {
+                        const int64_t off = dense ? ee[u] : static_cast<int64_t>(ee[u] / s) * a.ldo + ee[u] % s;
+                        store_out<4>(a, out, sm.ooff[we[u]] + off, v[u]);
                     }
                 }
             }
@@ -639,10 +680,14 @@ hipError_t launch_fast(const DecodeArgs& a, const DecodeSet& single, hipStream_t
     // of at least 64 elements (each workgroup repeats the small elimination),
     // which keeps the per-wave tile chains of a single decode short while the
     // repeated eliminations, one per workgroup on its first SIMD, stay few
-    // (one (32,24) set of 64 columns: 45.6 us with 2048 workgroups, 34.0 with
-    // 1024, 34.4 with 512, 40.9 with 256).
+    // (one (32,24) set of 64 columns: 23.0 us with 1024 workgroups, 23.5 with
+    // 512, 29 with 2048).  About 512 for a batch whose sets may miss more than
+    // four blocks, where the elimination weighs more (1000 (64,48) sets of
+    // 16384 x 8: 139 us with 512, 150 with 1024; 100 (16,12) sets of 2000 x
+    // 64: 28.7 and 26.1).
     const int64_t total = a.qb * a.s;
-    const int64_t want = std::max<int64_t>(1, ceil_div(1024, a.batch));
+    const int64_t target = a.batch > 1 && std::min(a.k, a.n - a.k) > 4 ? 512 : 1024;
+    const int64_t want = std::max<int64_t>(1, ceil_div(target, a.batch));
     const int64_t per = std::max<int64_t>(64, ceil_div(ceil_div(std::max<int64_t>(total, 1), want), 16) * 16);
     const int64_t chunks = std::max<int64_t>(1, ceil_div(total, per));
     const int64_t blocks = chunks * a.batch;

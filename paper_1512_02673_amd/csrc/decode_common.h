@@ -7,72 +7,73 @@
 namespace coded {
 namespace {
 
-__device__ inline int set_entry(const DecodeSet& s, int c) {
-    // Pick byte c of the packed set with constant-index reads of the argument.
-    uint32_t word = 0;
-#pragma unroll
-    for (int i = 0; i < kMaxN / 4; ++i) word = (c / 4 == i) ? s.packed[i] : word;
-    return static_cast<int>((word >> (8 * (c % 4))) & 0xFFu);
-}
-
 // Per-set bookkeeping in LDS.
 struct SetMeta {
-    int32_t raw[kMaxN];
+    uint64_t mask[kMaxN / 64]; // bit w: worker w survived
     int32_t S[kMaxN];          // sorted survivors
-    int32_t present[kMaxN];
+    int32_t present[kMaxN];    // the one-pass product only
     int32_t miss[kMaxN];       // missing systematic blocks, ascending
     int64_t yoff[kMaxN];       // element offset of survivor c's result in Y
     int64_t ooff[kMaxN];       // element offset of block j's first row in out
     int32_t lim[kMaxN];        // rows of block j that lie inside A (the rest is padding)
     int32_t status, m;
+    int32_t pivot;             // of an elimination step in LDS
 };
 
-// Reads set b, validates it (range, repeats), sorts it and fills the
-// bookkeeping.  Returns false (after writing info = -1) for an invalid set.
-// Every thread of the workgroup (NT threads) must call it.
+// Bits below position i of a 128-bit mask.
+__device__ inline int bits_below(uint64_t m0, uint64_t m1, int i) {
+    const uint64_t b0 = i >= 64 ? ~uint64_t{0} : (uint64_t{1} << i) - 1;
+    const uint64_t b1 = i > 64 ? (uint64_t{1} << (i - 64)) - 1 : 0;
+    return __popcll(m0 & b0) + __popcll(m1 & b1);
+}
+
+// Reads set b as a bit mask of the survivors (a single set comes as one),
+// validates it (range, repeats) and fills the bookkeeping: a worker's place
+// among the survivors, and a block's among the missing, is the count of mask
+// bits below it, so nothing is sorted and no loop walks the set.  Returns
+// false (after writing info = -1) for an invalid set.  Every thread of the
+// workgroup (NT >= 128 threads) must call it.
 template <int NT>
 __device__ __forceinline__ bool setup_set(const DecodeArgs& a, const DecodeSet& single, int64_t b, bool writer, SetMeta& sm) {
+    static_assert(NT >= kMaxN, "one thread per worker");
     const int tid = threadIdx.x;
     const int n = a.n, k = a.k;
+    uint64_t m0 = single.mask[0], m1 = single.mask[1];
     if (tid == 0) sm.status = 0;
-    for (int i = tid; i < n; i += NT) sm.present[i] = 0;
-    for (int c = tid; c < k; c += NT) sm.raw[c] = a.sets ? a.sets[b * k + c] : set_entry(single, c);
-    __syncthreads();
-    for (int c = tid; c < k; c += NT) {
-        const int v = sm.raw[c];
-        if (v < 0 || v >= n) {
-            sm.status = -1;
-            continue;
+    if (a.sets) {
+        if (tid == 0) sm.mask[0] = sm.mask[1] = 0;
+        __syncthreads();
+        if (tid < k) {
+            const int v = a.sets[b * k + tid];
+            if (v < 0 || v >= n)
+                sm.status = -1;
+            else
+                atomicOr(reinterpret_cast<unsigned long long*>(&sm.mask[v >> 6]), 1ull << (v & 63));
         }
-        int rank = 0, same = 0;
-        for (int j = 0; j < k; ++j) {
-            rank += sm.raw[j] < v;
-            same += sm.raw[j] == v;
+        __syncthreads();
+        m0 = sm.mask[0];
+        m1 = sm.mask[1];
+        // a repeated index leaves fewer than k bits
+        if (sm.status != 0 || __popcll(m0) + __popcll(m1) != k) {
+            if (writer) a.info[b] = -1;
+            return false;
         }
-        if (same != 1) {
-            sm.status = -1;
-            continue;
+    }
+    if (tid < n) {
+        const bool in = ((tid < 64 ? m0 >> tid : m1 >> (tid - 64)) & 1) != 0;
+        const int below = bits_below(m0, m1, tid);
+        if (in) {
+            sm.S[below] = tid;
+            sm.yoff[below] = static_cast<int64_t>(tid) * a.qb * a.s;
         }
-        sm.S[rank] = v;
-        sm.present[v] = 1;
+        if (tid < k) {
+            if (!in) sm.miss[tid - below] = tid;
+            sm.ooff[tid] = static_cast<int64_t>(tid) * a.qb * a.ldo;
+            const int64_t lim = a.q - static_cast<int64_t>(tid) * a.qb;
+            sm.lim[tid] = static_cast<int32_t>(lim < 0 ? 0 : (lim > a.qb ? a.qb : lim));
+        }
     }
-    __syncthreads();
-    if (sm.status != 0) {
-        if (writer) a.info[b] = sm.status;
-        return false;
-    }
-    if (tid == 0) {
-        int m = 0;
-        for (int j = 0; j < k; ++j)
-            if (!sm.present[j]) sm.miss[m++] = j;
-        sm.m = m;
-    }
-    for (int c = tid; c < k; c += NT) sm.yoff[c] = static_cast<int64_t>(sm.S[c]) * a.qb * a.s;
-    for (int j = tid; j < k; j += NT) {
-        sm.ooff[j] = static_cast<int64_t>(j) * a.qb * a.ldo;
-        const int64_t lim = a.q - static_cast<int64_t>(j) * a.qb;
-        sm.lim[j] = static_cast<int32_t>(lim < 0 ? 0 : (lim > a.qb ? a.qb : lim));
-    }
+    if (tid == 0) sm.m = k - bits_below(m0, m1, k);
     __syncthreads();
     return true;
 }

@@ -63,8 +63,7 @@ struct WorkerArgs {
 };
 hipError_t launch_worker_f32(const WorkerArgs& a, hipStream_t st);
 // fp32 with s > 1 on the fp64 matrix cores (worker_f32_mfma.hip); supported
-// when r and lda are multiples of 4, 0 < r <= 2^30 and A, parity are 16-byte
-// aligned.
+// when 4 <= r <= 2^30 and the lo plane, if any, is fp32.
 bool gemm_f32_mfma_supported(const WorkerArgs& a);
 hipError_t launch_gemm_f32_mfma(const WorkerArgs& a, hipStream_t st);
 hipError_t launch_worker_bf16(const WorkerArgs& a, hipStream_t st);
@@ -86,10 +85,10 @@ bool fused_bf16_supported(int n, int k, int planes, int64_t r, int64_t lda);
 hipError_t launch_fused_bf16(FusedArgs a, bool products, int compute_units, hipStream_t st);
 
 // ---------------------------------------------------------------- decode
-// One survivor set passed by value (worker indices < 128 fit in a byte;
-// packed four to a word so the kernel can pick them out of its arguments).
+// One survivor set passed by value, checked on the host: bit w of the mask is
+// set when worker w survived.
 struct DecodeSet {
-    uint32_t packed[kMaxN / 4];
+    uint64_t mask[kMaxN / 64];
 };
 struct DecodeArgs {
     const double* G;      // device n x k

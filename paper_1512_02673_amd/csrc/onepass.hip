@@ -64,8 +64,7 @@ __device__ inline double wave_total(double v) {
 // that precedes the decode.  Returns the number of missing blocks.
 __device__ inline int setup_set_wave(const OnePassArgs& a, int lane, SetMeta& sm) {
     const int n = a.n, k = a.k;
-    uint32_t mask = 0;
-    for (int c = 0; c < k; ++c) mask |= 1u << set_entry(a.set, c);
+    const uint32_t mask = static_cast<uint32_t>(a.set.mask[0]);
     const uint32_t below = static_cast<uint32_t>((uint64_t{1} << lane) - 1u);   // blocks below this lane's
     const bool in = lane < 32 && ((mask >> lane) & 1u) != 0;
     if (lane < n) {
