@@ -10,15 +10,21 @@
 // up to 16 * NCT (or 4 * NCT) columns of X.  For a systematic worker, or a
 // parity worker with one plane, slot rho is block row t0 + rho.  For a parity
 // worker with two planes, slot rho is row t0 + rho % (8 RT) of plane
-// rho / (8 RT): the hi and lo rows of a block row sit in one tile and their
-// results are added at the end, so every workgroup streams the same bytes
-// (two-plane rows as longer K loops would leave the parity workgroups running
-// alone at the end of the launch).
+// rho / (8 RT): the hi and lo rows of a block row sit in one tile, so every
+// workgroup streams the same bytes (two-plane rows as longer K loops would
+// leave the parity workgroups running alone at the end of the launch).  With
+// 32 columns the hi and lo elements are added as they are widened (24 + 24 bits
+// side by side fit a double) and multiply once, which halves the parity
+// workers' matrix work (16384 x 4096, 64 columns: 257 us against 235); tiles of
+// up to 16 columns, bound by HBM, add the results at the end.
 //
 // K loop.  K is walked in chunks of KC.  A chunk's slot rows are loaded with
 // 16-byte loads (KC/4 consecutive threads cover one row's KC contiguous
 // elements) into a ring of PF register sets, so PF chunks are in flight; the
-// chunk is then stored to a double-buffered LDS tile with 16-byte row padding
+// chunk (rows start at any fp32 boundary; TAIL: r is no multiple of 4, the
+// piece that would pass the row's end is read from the row's last four
+// elements and moved down before it is stored) is then stored to a
+// double-buffered LDS tile with 16-byte row padding
 // (conflict-free 16-byte reads down a column of rows), X's KC x SP slice is
 // stored transposed and widened to fp64, one barrier, and the load of chunk
 // c + PF is issued before the chunk is multiplied.  Every chunk, the last one
@@ -50,6 +56,8 @@
 // C[4((l % 16) / 4) + l / 16][l % 4] (4x4x4).  The k index a lane supplies
 // is free as long as A and B agree, so lane group g = l/16 takes the four
 // consecutive k of one 16-byte LDS read, one per instruction.
+#include <type_traits>
+
 #include "internal.h"
 #include "worker_common.h"
 
@@ -57,6 +65,7 @@ namespace coded {
 namespace {
 
 typedef float f32x4m __attribute__((ext_vector_type(4)));
+typedef f32x4m f32x4m_any __attribute__((aligned(4)));   // 16 bytes at any fp32 boundary
 typedef double f64x4m __attribute__((ext_vector_type(4)));
 
 constexpr int kMmThreads = 256;
@@ -83,7 +92,7 @@ struct MmCfg {
 };
 
 __device__ inline f32x4m load_stream4(const float* p) {
-    return __builtin_nontemporal_load(reinterpret_cast<const f32x4m*>(p));
+    return __builtin_nontemporal_load(reinterpret_cast<const f32x4m_any*>(p));
 }
 
 // Raw buffer resource over `bytes` bytes from `base` (no stride, no format:
@@ -94,9 +103,16 @@ __device__ inline __amdgpu_buffer_rsrc_t raw_buffer(const void* base, uint32_t b
 }
 constexpr int kAuxNonTemporal = 2;   // cache-policy bits of the load: nt
 
-template <int RT, int NCT, bool NARROW, int KC, int PF, bool BUF>
+// v moved down by sh (0..3) elements, zeros above.
+__device__ inline f32x4m shift_down(f32x4m v, int sh) {
+    if (sh & 1) v = f32x4m{v[1], v[2], v[3], 0.f};
+    if (sh & 2) v = f32x4m{v[2], v[3], 0.f, 0.f};
+    return v;
+}
+
+template <int RT, int NCT, bool NARROW, int KC, int PF, bool BUF, bool TAIL>
 __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a, int64_t stiles, int64_t ptiles,
-                                                                   int64_t c0) {
+                                                                   int64_t first_col) {
     using C = MmCfg<RT, NCT, NARROW, KC>;
     __shared__ __attribute__((aligned(16))) char smem[C::kLds];
     float* As = reinterpret_cast<float*>(smem);                // [2][kRows][kStride]
@@ -105,6 +121,8 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    const int64_t c0 = first_col + static_cast<int64_t>(blockIdx.y) * C::kSP;
 
     // Tile -> (worker, first block row); parity tiles first.
     const int64_t g = blockIdx.x;
@@ -180,9 +198,13 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
         abase = static_cast<const float*>(a.A) + static_cast<int64_t>(worker) * a.qb * a.lda;
         rows_in = a.q - static_cast<int64_t>(worker) * a.qb;
         rows_in = rows_in < a.qb ? rows_in : a.qb;
+        if (rows_in <= 0) {     // a block of padding only: read A's first row instead (stored as zeros)
+            abase = static_cast<const float*>(a.A);
+            rows_in = 1;
+        }
         rstride = a.lda;
         // the block's rows inside A, up to the last row's r-th column
-        abytes = static_cast<uint32_t>(rows_in > 0 ? ((rows_in - 1) * a.lda + a.r) * 4 : 0);
+        abytes = static_cast<uint32_t>(((rows_in - 1) * a.lda + a.r) * 4);
     }
     uint32_t aoff[C::kALoads];
 #pragma unroll
@@ -193,7 +215,21 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
         t = t > 0 ? t : 0;
         aoff[p] = static_cast<uint32_t>(((parity ? (rho / hrows) * plane_elems : 0) + t * rstride + acol[p]) * 4);
     }
-    const uint32_t xbytes = static_cast<uint32_t>(a.r * a.ldx * 4);
+    // TAIL: how far the last chunk's piece is moved back to end with the row
+    // (0 for a piece inside it, or wholly past it: that is stored as zeros),
+    // and its offset with the chunk's part in it.
+    int tail_sh[TAIL ? C::kALoads : 1];
+    uint32_t tail_off[TAIL ? C::kALoads : 1];
+    if constexpr (TAIL) {
+#pragma unroll
+        for (int p = 0; p < C::kALoads; ++p) {
+            const int kl = (nch - 1) * KC + acol[p];
+            tail_sh[p] = kl > r - 4 && kl < r ? kl - (r - 4) : 0;
+            tail_off[p] = aoff[p] + static_cast<uint32_t>((nch - 1) * KC - tail_sh[p]) * 4;
+        }
+    }
+    // the buffer ends with X's last element
+    const uint32_t xbytes = static_cast<uint32_t>(((a.r - 1) * a.ldx + a.s) * 4);
     const __amdgpu_buffer_rsrc_t rsA = raw_buffer(abase, abytes);
     const __amdgpu_buffer_rsrc_t rsX = raw_buffer(X, xbytes);
 
@@ -203,9 +239,12 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
             // scalar chunk offsets; past the last chunk, offsets beyond the buffers
             const uint32_t sa = live ? static_cast<uint32_t>(c) * KC * 4 : abytes;
             const uint32_t sx = live ? static_cast<uint32_t>(c) * KC * static_cast<uint32_t>(a.ldx) * 4 : xbytes;
+            const bool last = TAIL && c == nch - 1;
 #pragma unroll
             for (int p = 0; p < C::kALoads; ++p)
-                R[p] = __builtin_bit_cast(f32x4m, __builtin_amdgcn_raw_buffer_load_b128(rsA, aoff[p], sa, kAuxNonTemporal));
+                R[p] = __builtin_bit_cast(f32x4m, __builtin_amdgcn_raw_buffer_load_b128(
+                                                      rsA, last ? tail_off[TAIL ? p : 0] : aoff[p], last ? 0 : sa,
+                                                      kAuxNonTemporal));
 #pragma unroll
             for (int i = 0; i < C::kXLoads; ++i)
                 XR[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsX, xoff[i], sx, 0));
@@ -214,7 +253,7 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
 #pragma unroll
         for (int p = 0; p < C::kALoads; ++p) {
             int kk = c * KC + acol[p];
-            kk = kk < r ? kk : r - 4;
+            kk = kk < r - 4 ? kk : r - 4;
             R[p] = load_stream4(live ? gp[p] + kk : dummy);
         }
 #pragma unroll
@@ -237,7 +276,9 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
         }
 #pragma unroll
         for (int p = 0; p < C::kALoads; ++p)
-            *reinterpret_cast<f32x4m*>(Ab + ofs_a[p]) = acol[p] < kvalid ? R[p] : f32x4m{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4m*>(Ab + ofs_a[p]) =
+                acol[p] < kvalid ? (TAIL && kvalid < KC ? shift_down(R[p], tail_sh[TAIL ? p : 0]) : R[p])
+                                 : f32x4m{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < C::kXLoads; ++i) Xb[ofs_x[i]] = xk[i] < kvalid ? static_cast<double>(XR[i]) : 0.0;
     };
@@ -253,7 +294,10 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
             accn[rt][ct] = 0.0;
             accw[rt][ct] = f64x4m{0.0, 0.0, 0.0, 0.0};
         }
-    auto multiply = [&](int buf) {
+    // MERGE: row tile 1 holds the lo rows of row tile 0's block rows.
+    auto multiply = [&](int buf, auto merge) {
+        constexpr bool MERGE = decltype(merge)::value;
+        constexpr int NRT = MERGE ? 1 : RT;
         const float* Ab = As + buf * C::kRows * C::kStride;
         const double* Xb = Xs + buf * C::kSP * C::kXStride;
 #pragma unroll
@@ -276,8 +320,9 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
                 double ad[RT];
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) ad[rt] = static_cast<double>(af[rt][e]);
+                if constexpr (MERGE) ad[0] += ad[RT - 1];
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
+                for (int rt = 0; rt < NRT; ++rt)
 #pragma unroll
                     for (int ct = 0; ct < NCT; ++ct) {
                         if constexpr (NARROW)
@@ -289,28 +334,40 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
         }
     };
 
+    const bool pair = hrows != C::kRows;
+    constexpr bool kMerge = RT == 2 && NCT > 1;
     f32x4m aring[PF][C::kALoads];
     float xring[PF][C::kXLoads];
-    if (nch > 0) {
+    auto sweep = [&](auto merge) {
+        if (nch > 0) {
 #pragma unroll
-        for (int j = 0; j < PF; ++j) load_chunk(j, aring[j], xring[j]);
-    }
-    for (int cb = 0; cb < nch; cb += PF) {
-#pragma unroll
-        for (int j = 0; j < PF; ++j) {
-            const int c = cb + j;
-            if (c >= nch) break;
-            const int buf = c & 1;
-            store_chunk(buf, r - c * KC, aring[j], xring[j]);
-            __syncthreads();
-            load_chunk(c + PF, aring[j], xring[j]);
-            multiply(buf);
+            for (int j = 0; j < PF; ++j) load_chunk(j, aring[j], xring[j]);
         }
+        for (int cb = 0; cb < nch; cb += PF) {
+#pragma unroll
+            for (int j = 0; j < PF; ++j) {
+                const int c = cb + j;
+                if (c >= nch) break;
+                const int buf = c & 1;
+                store_chunk(buf, r - c * KC, aring[j], xring[j]);
+                __syncthreads();
+                load_chunk(c + PF, aring[j], xring[j]);
+                multiply(buf, merge);
+            }
+        }
+    };
+    if constexpr (kMerge) {
+        if (pair)
+            sweep(std::true_type{});
+        else
+            sweep(std::false_type{});
+    } else {
+        sweep(std::false_type{});
     }
 
     // Add the four waves' partial sums (wave 0, 1, 2, 3 in that order) and,
-    // for a two-plane parity tile, the lo rows to the hi rows, kRedCols
-    // columns per pass; padding rows of a systematic block are stored as 0.
+    // for a two-plane parity tile not merged before, the lo rows to the hi
+    // rows, kRedCols columns per pass; padding rows of a systematic block are stored as 0.
     constexpr int kPasses = C::kSP / C::kRedCols;
     const int w = C::kRows * C::kRedCols;
 #pragma unroll
@@ -335,7 +392,7 @@ __global__ __launch_bounds__(kMmThreads) void gemm_f32_mfma_kernel(WorkerArgs a,
             if (t >= a.qb || cc >= a.s) continue;
             const int o = row * C::kRedCols + col;
             double v = ((Red[o] + Red[w + o]) + Red[2 * w + o]) + Red[3 * w + o];
-            if (hrows != C::kRows) {
+            if (!kMerge && pair) {
                 const int o2 = o + hrows * C::kRedCols;
                 v += ((Red[o2] + Red[w + o2]) + Red[2 * w + o2]) + Red[3 * w + o2];
             }
@@ -356,35 +413,48 @@ bool buffer_offsets_fit(const WorkerArgs& a) {
 }
 
 template <int RT, int NCT, bool NARROW, int KC, int PF>
-hipError_t launch_mm(const WorkerArgs& a, int64_t c0, hipStream_t st) {
+hipError_t launch_mm(const WorkerArgs& a, int64_t c0, hipStream_t st, int64_t col_tiles = 1) {
     using C = MmCfg<RT, NCT, NARROW, KC>;
     const int64_t stiles = ceil_div(a.qb, C::kRows);
     const int64_t ptiles = a.planes == 2 ? ceil_div(a.qb, C::kRows / 2) : stiles;
     const int64_t blocks = stiles * a.n_sys + ptiles * a.n_par;
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    auto go = [&](auto buf, auto tail) {
+        hipLaunchKernelGGL((gemm_f32_mfma_kernel<RT, NCT, NARROW, KC, PF, decltype(buf)::value, decltype(tail)::value>),
+                           dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(col_tiles)), dim3(kMmThreads), 0,
+                           st, a, stiles, ptiles, c0);
+    };
+    auto go2 = [&](auto buf) { a.r % 4 ? go(buf, std::true_type{}) : go(buf, std::false_type{}); };
     if (buffer_offsets_fit(a))
-        hipLaunchKernelGGL((gemm_f32_mfma_kernel<RT, NCT, NARROW, KC, PF, true>), dim3(static_cast<unsigned>(blocks)),
-                           dim3(kMmThreads), 0, st, a, stiles, ptiles, c0);
+        go2(std::true_type{});
     else
-        hipLaunchKernelGGL((gemm_f32_mfma_kernel<RT, NCT, NARROW, KC, PF, false>),
-                           dim3(static_cast<unsigned>(blocks)), dim3(kMmThreads), 0, st, a, stiles, ptiles, c0);
+        go2(std::false_type{});
     return hipGetLastError();
 }
 
 }  // namespace
 
 bool gemm_f32_mfma_supported(const WorkerArgs& a) {
-    // K positions are 32-bit inside the kernel; rows need 16-byte alignment;
-    // planes are fp32 (a bfloat16 lo plane takes the general kernel).
-    return a.s > 1 && !a.lo_bf16 && a.r > 0 && a.r % 4 == 0 && a.r <= (1ll << 30) && a.lda % 4 == 0 &&
-           (reinterpret_cast<uintptr_t>(a.A) & 15u) == 0 && (reinterpret_cast<uintptr_t>(a.parity) & 15u) == 0;
+    // K positions are 32-bit inside the kernel; a row holds one 16-byte
+    // piece; planes are fp32 (a bfloat16 lo plane takes the general kernel).
+    return a.s > 1 && !a.lo_bf16 && a.r >= 4 && a.r <= (1ll << 30);
 }
 
 // Up to 8 columns: 4-column tiles, one launch.  More: 16-column tiles in
 // launches of at most 32 columns (two 32-column launches measured faster
 // than one 64-column launch at s = 64: the wider tile halves occupancy).
+// Few rows (fewer than 256 workgroups of 32 rows): the K loop of one workgroup
+// bounds the call, so tiles of 16 rows x 16 columns (or x 4, 256 k per chunk),
+// all columns in one launch, and four chunks in flight.  A (3,2) code on 777 x
+// 16000, 33 columns: 134 us against 372; (32,24), 100 x 8000, 40 columns: 44
+// against 175; (4,2), 64 x 16000, 8 columns: 44 against 70; at 768 workgroups
+// ((20,16), 16384 x 4096, 64 columns) 376 against 237.
 hipError_t launch_gemm_f32_mfma(const WorkerArgs& a, hipStream_t st) {
+    const int64_t rows = a.qb * (a.n_sys + (a.planes == 2 ? 2 : 1) * a.n_par);
+    if (rows < 256 * 32 && ceil_div(a.s, 4) <= 65535)
+        return a.s <= 8 ? launch_mm<1, 1, true, 256, 4>(a, 0, st, ceil_div(a.s, 4))
+                        : launch_mm<1, 1, false, 128, 4>(a, 0, st, ceil_div(a.s, 16));
     if (a.s <= 4) return launch_mm<1, 1, true, 128, 4>(a, 0, st);
     if (a.s <= 8) return launch_mm<1, 2, true, 128, 2>(a, 0, st);
     for (int64_t c0 = 0; c0 < a.s; c0 += 32) {
