@@ -10,6 +10,13 @@
 // to kGroup parity accumulators in registers; the sum runs over j in order.  Parity rows beyond kGroup are
 // handled by further groups (grid.y), each re-reading A.
 //
+// Rows start at any element boundary and have any length: a thread's vector
+// (VEC columns) that would pass the row's end is moved back to end with it, so
+// the last two threads of a row form some columns twice, with the same values.
+// A row of fewer than 256 vectors takes only as many threads, and a workgroup
+// several rows ((3,2) on 300000 x 200: 242 us with one row each, 120 here; bf16
+// 184 and 49; (25,23) on 11500 x 5750, scalar loads 76, here 57).
+//
 // Storage: with planes == 2 the exact sum (fp64 for fp32 inputs, fp32 for
 // bf16 inputs) is stored as hi = round(sum) and lo = round(sum - hi).
 #include "internal.h"
@@ -28,12 +35,28 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
 }
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
 
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u32x4e __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned int u32x2e __attribute__((ext_vector_type(2), aligned(2)));
+
+// Threads per block row (a workgroup takes kThreads / that many rows).
+int row_threads(int64_t r, int vec) {
+    const int64_t v = ceil_div(r, vec);
+    return v < kThreads ? static_cast<int>(v) : kThreads;
+}
+
 // One thread: VEC consecutive columns of block row t, parity rows
 // [p0, p0 + np) with np <= kGroup.
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int64_t col_chunks) {
+__global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int64_t col_chunks, int width) {
     __shared__ double sP[kGroup * kMaxN];
-    const int64_t t = blockIdx.x;
+    int64_t t = blockIdx.x;
+    int lane = threadIdx.x;
+    if (width < kThreads) {               // several rows: this thread's row and place in it
+        const int per = kThreads / width, row = lane / width;
+        t = t * per + row;
+        lane = row < per ? lane - row * width : kThreads;
+    }
     const int64_t chunk = blockIdx.y % col_chunks;
     const int p0 = static_cast<int>(blockIdx.y / col_chunks) * kGroup;
     const int npar = a.n - a.k;
@@ -44,8 +67,9 @@ __global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int6
         sP[p * k + j] = a.G[(a.k + p0 + p) * k + j];
     }
     __syncthreads();
-    const int64_t c = (chunk * kThreads + threadIdx.x) * VEC;
-    if (c >= a.r) return;
+    int64_t c = (chunk * kThreads + lane) * VEC;
+    if (c >= a.r || t >= a.qb) return;
+    c = min(c, a.r - VEC);
     const float* A = static_cast<const float*>(a.A);
 
     double acc[kGroup][VEC];
@@ -64,7 +88,7 @@ __global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int6
             const int j = min(j0 + u, kv - 1);   // past the last block: re-read it, not used
             const float* src = A + (static_cast<int64_t>(j) * a.qb + t) * a.lda + c;
             if constexpr (VEC == 4) {
-                const float4 f = *reinterpret_cast<const float4*>(src);
+                const f32x4e f = *reinterpret_cast<const f32x4e*>(src);
                 v4[u][0] = f.x; v4[u][1] = f.y; v4[u][2] = f.z; v4[u][3] = f.w;
             } else {
 #pragma unroll
@@ -101,15 +125,15 @@ __global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int6
         const int64_t off = (static_cast<int64_t>(p0 + p) * a.qb + t) * a.r + c;
         float* dst = par + off;
         if constexpr (VEC == 4) {
-            *reinterpret_cast<float4*>(dst) = make_float4(hi[0], hi[1], hi[2], hi[3]);
+            *reinterpret_cast<f32x4e*>(dst) = f32x4e{hi[0], hi[1], hi[2], hi[3]};
             if (a.planes == 2) {
                 if (a.lo_bf16) {
-                    uint2 l;
+                    u32x2e l;
                     l.x = f32_to_bf16_rne(lo[0]) | (static_cast<uint32_t>(f32_to_bf16_rne(lo[1])) << 16);
                     l.y = f32_to_bf16_rne(lo[2]) | (static_cast<uint32_t>(f32_to_bf16_rne(lo[3])) << 16);
-                    *reinterpret_cast<uint2*>(par16 + off) = l;
+                    *reinterpret_cast<u32x2e*>(par16 + off) = l;
                 } else {
-                    *reinterpret_cast<float4*>(dst + plane) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+                    *reinterpret_cast<f32x4e*>(dst + plane) = f32x4e{lo[0], lo[1], lo[2], lo[3]};
                 }
             }
         } else {
@@ -130,9 +154,15 @@ __global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int6
 // bf16: products of two bf16 values are exact in fp32; the k-term sum is
 // accumulated in fp32 and split into bf16 hi + lo.
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int64_t col_chunks) {
+__global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int64_t col_chunks, int width) {
     __shared__ float sP[kGroup * kMaxN];
-    const int64_t t = blockIdx.x;
+    int64_t t = blockIdx.x;
+    int lane = threadIdx.x;
+    if (width < kThreads) {               // several rows: this thread's row and place in it
+        const int per = kThreads / width, row = lane / width;
+        t = t * per + row;
+        lane = row < per ? lane - row * width : kThreads;
+    }
     const int64_t chunk = blockIdx.y % col_chunks;
     const int p0 = static_cast<int>(blockIdx.y / col_chunks) * kGroup;
     const int npar = a.n - a.k;
@@ -143,8 +173,9 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int
         sP[p * k + j] = static_cast<float>(a.G[(a.k + p0 + p) * k + j]);
     }
     __syncthreads();
-    const int64_t c = (chunk * kThreads + threadIdx.x) * VEC;
-    if (c >= a.r) return;
+    int64_t c = (chunk * kThreads + lane) * VEC;
+    if (c >= a.r || t >= a.qb) return;
+    c = min(c, a.r - VEC);
     const uint16_t* A = static_cast<const uint16_t*>(a.A);
 
     float acc[kGroup][VEC];
@@ -161,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int
             const int j = min(j0 + u, kv - 1);   // past the last block: re-read it, not used
             const uint16_t* src = A + (static_cast<int64_t>(j) * a.qb + t) * a.lda + c;
             if constexpr (VEC == 8) {
-                const uint4 q4 = *reinterpret_cast<const uint4*>(src);
+                const u32x4e q4 = *reinterpret_cast<const u32x4e*>(src);
                 const uint32_t w[4] = {q4.x, q4.y, q4.z, q4.w};
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
@@ -200,13 +231,13 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int
         }
         uint16_t* dst = par + (static_cast<int64_t>(p0 + p) * a.qb + t) * a.r + c;
         if constexpr (VEC == 8) {
-            uint4 h4, l4;
+            u32x4e h4, l4;
             h4.x = hi[0] | (uint32_t(hi[1]) << 16); h4.y = hi[2] | (uint32_t(hi[3]) << 16);
             h4.z = hi[4] | (uint32_t(hi[5]) << 16); h4.w = hi[6] | (uint32_t(hi[7]) << 16);
             l4.x = lo[0] | (uint32_t(lo[1]) << 16); l4.y = lo[2] | (uint32_t(lo[3]) << 16);
             l4.z = lo[4] | (uint32_t(lo[5]) << 16); l4.w = lo[6] | (uint32_t(lo[7]) << 16);
-            *reinterpret_cast<uint4*>(dst) = h4;
-            if (a.planes == 2) *reinterpret_cast<uint4*>(dst + plane) = l4;
+            *reinterpret_cast<u32x4e*>(dst) = h4;
+            if (a.planes == 2) *reinterpret_cast<u32x4e*>(dst + plane) = l4;
         } else {
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
@@ -217,23 +248,23 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int
     }
 }
 
-bool aligned(const void* p, int bytes) { return (reinterpret_cast<uintptr_t>(p) % bytes) == 0; }
-
 }  // namespace
 
 hipError_t launch_encode_f32(const EncodeArgs& a, hipStream_t st) {
     const int npar = a.n - a.k;
     if (npar == 0 || a.qb == 0 || a.r == 0) return hipSuccess;
     const int groups = static_cast<int>(ceil_div(npar, kGroup));
-    const bool vec = (a.r % 4 == 0) && (a.lda % 4 == 0) && aligned(a.A, 16) && aligned(a.parity, 16);
+    const bool vec = a.r >= 4;
     const int V = vec ? 4 : 1;
     const int64_t chunks = ceil_div(a.r, static_cast<int64_t>(kThreads) * V);
     if (chunks * groups > 65535) return hipErrorInvalidConfiguration;
-    dim3 grid(static_cast<unsigned>(a.qb), static_cast<unsigned>(chunks * groups));
+    const int width = row_threads(a.r, V);
+    const int64_t rows = ceil_div(a.qb, kThreads / width);
+    dim3 grid(static_cast<unsigned>(rows), static_cast<unsigned>(chunks * groups));
     if (vec)
-        hipLaunchKernelGGL(encode_f32_kernel<4>, grid, dim3(kThreads), 0, st, a, chunks);
+        hipLaunchKernelGGL(encode_f32_kernel<4>, grid, dim3(kThreads), 0, st, a, chunks, width);
     else
-        hipLaunchKernelGGL(encode_f32_kernel<1>, grid, dim3(kThreads), 0, st, a, chunks);
+        hipLaunchKernelGGL(encode_f32_kernel<1>, grid, dim3(kThreads), 0, st, a, chunks, width);
     return hipGetLastError();
 }
 
@@ -241,15 +272,17 @@ hipError_t launch_encode_bf16(const EncodeArgs& a, hipStream_t st) {
     const int npar = a.n - a.k;
     if (npar == 0 || a.qb == 0 || a.r == 0) return hipSuccess;
     const int groups = static_cast<int>(ceil_div(npar, kGroup));
-    const bool vec = (a.r % 8 == 0) && (a.lda % 8 == 0) && aligned(a.A, 16) && aligned(a.parity, 16);
+    const bool vec = a.r >= 8;
     const int V = vec ? 8 : 1;
     const int64_t chunks = ceil_div(a.r, static_cast<int64_t>(kThreads) * V);
     if (chunks * groups > 65535) return hipErrorInvalidConfiguration;
-    dim3 grid(static_cast<unsigned>(a.qb), static_cast<unsigned>(chunks * groups));
+    const int width = row_threads(a.r, V);
+    const int64_t rows = ceil_div(a.qb, kThreads / width);
+    dim3 grid(static_cast<unsigned>(rows), static_cast<unsigned>(chunks * groups));
     if (vec)
-        hipLaunchKernelGGL(encode_bf16_kernel<8>, grid, dim3(kThreads), 0, st, a, chunks);
+        hipLaunchKernelGGL(encode_bf16_kernel<8>, grid, dim3(kThreads), 0, st, a, chunks, width);
     else
-        hipLaunchKernelGGL(encode_bf16_kernel<1>, grid, dim3(kThreads), 0, st, a, chunks);
+        hipLaunchKernelGGL(encode_bf16_kernel<1>, grid, dim3(kThreads), 0, st, a, chunks, width);
     return hipGetLastError();
 }
 
