@@ -21,11 +21,9 @@
 // no global scratch or second launch is needed; the arithmetic is identical
 // in every workgroup, so results are deterministic.
 //
-// Apply: a thread takes E consecutive elements of a block row (E = 4 when a
-// row's columns come in aligned groups of four, so every output goes out as
-// one 16-byte store; E = 1 otherwise, lanes on consecutive elements) and
-// computes the missing outputs PASS at a time in registers; each pair of D
-// entries read from LDS feeds 2*E fused multiply-adds.
+// E = 4 when a row's columns come in aligned groups of four or the rows lie
+// one after another, so that outputs go out as 16-byte stores; E = 1
+// otherwise, lanes on consecutive elements.
 #include "internal.h"
 #include "decode_common.h"
 
@@ -35,41 +33,31 @@ namespace {
 constexpr int kThreads = 256;
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef f32x4v f32x4v_any __attribute__((aligned(4)));     // 16 bytes at any fp32 boundary
+typedef double f64x2v __attribute__((ext_vector_type(2)));
+typedef f64x2v f64x2v_any __attribute__((aligned(8)));     // 16 bytes at any fp64 boundary
 
-template <int E, typename YT>
-struct Vec;
-template <>
-struct Vec<1, double> {
-    __device__ static void load(const double* p, double* y) { y[0] = p[0]; }
-};
-template <>
-struct Vec<4, double> {
-    __device__ static void load(const double* p, double* y) {
-        const double2 lo = reinterpret_cast<const double2*>(p)[0], hi = reinterpret_cast<const double2*>(p)[1];
-        y[0] = lo.x; y[1] = lo.y; y[2] = hi.x; y[3] = hi.y;
-    }
-};
-template <>
-struct Vec<1, float> {
-    __device__ static void load(const float* p, double* y) { y[0] = p[0]; }
-};
-template <>
-struct Vec<4, float> {
-    __device__ static void load(const float* p, double* y) {
-        const float4 v = *reinterpret_cast<const float4*>(p);
-        y[0] = v.x; y[1] = v.y; y[2] = v.z; y[3] = v.w;
-    }
-};
+// ANY: at any boundary of the type, else 16-byte aligned.
+template <bool ANY>
+__device__ inline f32x4v load4(const float* p) {
+    if constexpr (ANY) return *reinterpret_cast<const f32x4v_any*>(p);
+    return *reinterpret_cast<const f32x4v*>(p);
+}
+template <bool ANY>
+__device__ inline f64x2v load2(const double* p) {
+    if constexpr (ANY) return *reinterpret_cast<const f64x2v_any*>(p);
+    return *reinterpret_cast<const f64x2v*>(p);
+}
 
 // out = v, or alpha * v + beta * c when an epilogue operand is given (c has
 // out's layout; the element is read before it is written, so c may be out).
-template <int E, typename T>
+template <int E, bool ANY = true, typename T>
 __device__ inline void store_out(const DecodeArgs& a, float* p, int64_t off, const T* v) {
     float w[E];
     if (a.c) {
         float cv[E];
         if constexpr (E == 4) {
-            const float4 f = *reinterpret_cast<const float4*>(a.c + off);
+            const f32x4v f = load4<ANY>(a.c + off);
             cv[0] = f.x; cv[1] = f.y; cv[2] = f.z; cv[3] = f.w;
         } else {
             cv[0] = a.c[off];
@@ -84,7 +72,10 @@ __device__ inline void store_out(const DecodeArgs& a, float* p, int64_t off, con
     // decoded outputs are written once and not read again here: non-temporal
     if constexpr (E == 4) {
         const f32x4v q = {w[0], w[1], w[2], w[3]};
-        __builtin_nontemporal_store(q, reinterpret_cast<f32x4v*>(p + off));
+        if constexpr (ANY)
+            __builtin_nontemporal_store(q, reinterpret_cast<f32x4v_any*>(p + off));
+        else
+            __builtin_nontemporal_store(q, reinterpret_cast<f32x4v*>(p + off));
     } else {
         __builtin_nontemporal_store(w[0], p + off);
     }
@@ -92,13 +83,13 @@ __device__ inline void store_out(const DecodeArgs& a, float* p, int64_t off, con
 
 // E consecutive elements of Y as fp32 (a copied systematic block is the
 // worker's result rounded to the output type).
-template <int E, typename YT>
+template <int E, typename YT, bool ANY = true>
 __device__ inline void load_f32(const YT* p, float* v) {
     if constexpr (E == 4 && sizeof(YT) == 4) {
-        const float4 f = *reinterpret_cast<const float4*>(p);
+        const f32x4v f = load4<ANY>(p);
         v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
     } else if constexpr (E == 4) {
-        const double2 lo = reinterpret_cast<const double2*>(p)[0], hi = reinterpret_cast<const double2*>(p)[1];
+        const f64x2v lo = load2<ANY>(p), hi = load2<ANY>(p + 2);
         v[0] = static_cast<float>(lo.x); v[1] = static_cast<float>(lo.y);
         v[2] = static_cast<float>(hi.x); v[3] = static_cast<float>(hi.y);
     } else {
@@ -106,160 +97,259 @@ __device__ inline void load_f32(const YT* p, float* v) {
     }
 }
 
-// PASS: missing outputs computed per sweep over the survivors (register
-// bucket); E: elements per thread; ST (>= every m of the launch, even) is the
-// row stride of the LDS matrices, sized on the host.
-template <int PASS, int E, typename YT>
-__global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a, DecodeSet single, int64_t chunks,
-                                                          int elems_per_block, int ST) {
-    __shared__ SetMeta sm;
-    extern __shared__ __align__(16) double dyn[];
-    double* sD = dyn;                    // D column-major: sD[c * ST + b], c < k
-    double* sMat = dyn + a.k * ST;       // m x m, row stride ST
-    double* sL = sMat + ST * ST;         // multipliers of one elimination step
+// The last, incomplete group of four of a block whose rows lie one after
+// another: y and off belong to its first element, `left` < 4 remain.
+template <typename YT>
+__device__ __forceinline__ void copy_tail(const DecodeArgs& a, float* p, int64_t off, const YT* y, int left) {
+    for (int i = 0; i < left; ++i) {
+        const float v = static_cast<float>(y[i]);
+        store_out<1>(a, p, off + i, &v);
+    }
+}
 
-    const int tid = threadIdx.x;
+// Largest of a 32-bit value over the wave, in every lane.
+__device__ inline uint32_t wave_max_u32(uint32_t v) {
+#define CODED_MAX_DPP(CTRL, ROWS)                                                                                    \
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false)))
+    CODED_MAX_DPP(0x111, 0xF);           // lane - 1, - 2, - 4, - 8 of a row of 16
+    CODED_MAX_DPP(0x112, 0xF);
+    CODED_MAX_DPP(0x114, 0xF);
+    CODED_MAX_DPP(0x118, 0xF);
+    CODED_MAX_DPP(0x142, 0xA);           // the row before into rows 1 and 3
+    CODED_MAX_DPP(0x143, 0xC);           // the lower half into the upper
+#undef CODED_MAX_DPP
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+typedef double f64x4v __attribute__((ext_vector_type(4)));
+
+// Codes wider than the register elimination below (m + k > 64, or m > 16),
+// and results past 2^31 elements.
+//
+// Elimination: four threads hold each column of the m x (m + k) system (m + k
+// <= n <= 128) in registers, every fourth row each, and mirror it in LDS.
+// Gauss-Jordan without row exchanges: every wave reads column j, one row per
+// lane, finds the pivot among the unused rows and divides all multipliers at
+// once, so a step is one barrier and no serial search.  Bound by the latency
+// of its m dependent steps.  (An LU in LDS with one thread's pivot search and
+// five barriers a step took (128,96) to 210 us a call whatever its size; the
+// same steps on LDS operands, two threads a column, 57; this 36.  1000 sets
+// of 65536 x 1: 716 and 220 us.)
+//
+// Combination: out[M] += D (16 rows a tile) * Y on v_mfma_f64_16x16x4f64, 32
+// elements per wave, the survivors' loads issued eight at a time and used for
+// all row tiles (one sweep over Y instead of one per eight missing blocks).
+// Every workgroup of a set repeats the elimination; RT row tiles hold any m
+// of the launch.  Neither RT nor the chunks change a result.
+constexpr int kWideThreads = 512;
+
+template <int RT, int E, typename YT>
+__global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a, DecodeSet single, int64_t chunks,
+                                                               int elems_per_block, int LD) {
+    __shared__ SetMeta sm;
+    extern __shared__ __align__(16) double sA[];     // column c at sA[c * LD], LD odd, rows 0 .. m-1
+    constexpr int kThreads = kWideThreads, kWaves = kThreads / 64;
+    constexpr int kParts = kThreads / kMaxN, HR = 16 * RT / kParts;
+    static_assert(kThreads % kMaxN == 0 && 16 * RT % kParts == 0, "whole columns per part");
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int k = a.k;
     const int64_t b = blockIdx.x / chunks;
     const int64_t chunk = blockIdx.x % chunks;
     const bool writer = (chunk == 0 && tid == 0);
     if (!setup_set<kThreads>(a, single, b, writer, sm)) return;
-    const int32_t* sS = sm.S;
-    const int32_t* sMiss = sm.miss;
-    const int64_t* sYoff = sm.yoff;
-    const int64_t* sOoff = sm.ooff;
-    const int32_t* sLim = sm.lim;
     const int m = sm.m;
     const int first_par = k - m;          // sorted: systematic survivors first, then parity
 
     if (m > 0) {
-        // sMat[r][cb] = G[S_par[r]][M[cb]];  column c of D starts as column c
-        // of the right-hand side [-G[S_par, S_sys] | I]; rows >= m stay 0.
-        for (int e = tid; e < m * m; e += kThreads) {
-            const int ra = e / m, cb = e % m;
-            sMat[ra * ST + cb] = a.G[static_cast<int64_t>(sS[first_par + ra]) * k + sMiss[cb]];
-        }
-        for (int e = tid; e < ST * k; e += kThreads) {
-            const int c = e / ST, ra = e % ST;
-            double v = 0.0;
-            if (ra < m) {
-                const int sc = sS[c];
-                v = sc < k ? -a.G[static_cast<int64_t>(sS[first_par + ra]) * k + sc]
-                           : ((c - first_par == ra) ? 1.0 : 0.0);
+        // this thread's column, 0 .. m-1: G[S_par, M], then [-G[S_par, S_sys] | I],
+        // and its rows part, part + kParts, ..
+        const int c = tid % kMaxN;
+        const int part = __builtin_amdgcn_readfirstlane(tid / kMaxN);
+        const bool mine = c < m + k;
+        double* mirror = sA + (mine ? c * LD : 0);
+        double col[HR];
+        {
+            const int sc = !mine ? 0 : (c < m ? sm.miss[c] : sm.S[c - m]);
+#pragma unroll
+            for (int i = 0; i < HR; ++i) {
+                const int row = kParts * i + part;
+                col[i] = row < m && sc < k ? a.G[static_cast<int64_t>(sm.S[first_par + row]) * k + sc] : 0.0;
             }
-            sD[c * ST + ra] = v;
+#pragma unroll
+            for (int i = 0; i < HR; ++i) {
+                const int row = kParts * i + part;
+                if (c >= m) col[i] = sc < k ? -col[i] : (c - m - first_par == row ? 1.0 : 0.0);
+                if (mine && row < m) mirror[row] = col[i];
+            }
         }
         __syncthreads();
 
-        // Gaussian elimination with partial pivoting on sMat, applied to the
-        // right-hand sides as it goes.
+        uint64_t unused = m == 64 ? ~uint64_t{0} : (uint64_t{1} << m) - 1;   // rows that were no pivot yet
+        int place = 0;                    // of row `lane`: the column it was the pivot of, and the pivot
+        double pivot = 1.0;
+        int bad = 0;
         for (int j = 0; j < m; ++j) {
-            if (tid == 0) {
-                int p = j;
-                double best = fabs(sMat[j * ST + j]);
-                for (int i = j + 1; i < m; ++i) {
-                    const double v = fabs(sMat[i * ST + j]);
-                    if (v > best) {
-                        best = v;
-                        p = i;
-                    }
-                }
-                if (best == 0.0) sm.status = first_par + j + 1;
-                sm.pivot = p;
+            const double v = lane < m ? sA[j * LD + lane] : 0.0;
+            // pivot: largest |entry| of the unused rows, lowest row on ties
+            // (positive doubles order like their bits, high word first)
+            const bool open = (unused >> lane) & 1;
+            const uint64_t u = static_cast<uint64_t>(__double_as_longlong(fabs(v)));
+            const uint32_t hi = open ? static_cast<uint32_t>(u >> 32) : 0u;
+            const uint32_t top = wave_max_u32(hi);
+            uint64_t cand = __ballot(open && hi == top);
+            if (cand & (cand - 1)) {
+                const bool in = (cand >> lane) & 1;
+                const uint32_t lo = in ? static_cast<uint32_t>(u) : 0u;
+                const uint32_t lotop = wave_max_u32(lo);
+                cand = __ballot(in && lo == lotop);
             }
-            __syncthreads();
-            if (sm.status != 0) break;
-            const int p = sm.pivot;
-            if (p != j) {
-                for (int c = tid; c < m; c += kThreads) {
-                    const double t0 = sMat[j * ST + c];
-                    sMat[j * ST + c] = sMat[p * ST + c];
-                    sMat[p * ST + c] = t0;
-                }
-                for (int c = tid; c < k; c += kThreads) {
-                    const double t0 = sD[c * ST + j];
-                    sD[c * ST + j] = sD[c * ST + p];
-                    sD[c * ST + p] = t0;
-                }
+            const int p = __builtin_ctzll(cand);
+            const double x = mirror[p];
+            const double piv = lane_value(v, p);
+            if (piv == 0.0) {             // the same in every wave
+                bad = first_par + j + 1;
+                break;
             }
-            __syncthreads();
-            for (int i = j + 1 + tid; i < m; i += kThreads) sL[i] = sMat[i * ST + j] / sMat[j * ST + j];
-            __syncthreads();
-            const int rows = m - j - 1;
-            if (rows > 0) {
-                for (int e = tid; e < rows * rows; e += kThreads) {
-                    const int i = j + 1 + e / rows, c = j + 1 + e % rows;
-                    sMat[i * ST + c] -= sL[i] * sMat[j * ST + c];
-                }
-                // consecutive threads walk down a column of D (contiguous in LDS)
-                for (int e = tid; e < rows * k; e += kThreads) {
-                    const int c = e / rows, i = j + 1 + e % rows;
-                    sD[c * ST + i] -= sL[i] * sD[c * ST + j];
+            const double l = lane == p ? 0.0 : v / piv;
+            unused &= ~(uint64_t{1} << p);
+            if (lane == p) {
+                place = j;
+                pivot = piv;
+            }
+            const bool live = mine && c > j;
+#pragma unroll
+            for (int i = 0; i < HR; ++i) {
+                const int row = kParts * i + part;
+                if (row < m) {
+                    const double nv = fma(-lane_value(l, row), x, col[i]);
+                    col[i] = row == p ? col[i] : nv;
+                    if (live) mirror[row] = col[i];
                 }
             }
-            __syncthreads();
+            __syncthreads();              // this step's rows before the next column is read
         }
-        if (sm.status != 0) {
-            if (writer) a.info[b] = sm.status;
+        if (bad != 0) {
+            if (writer) a.info[b] = bad;
             return;
         }
-        // Back substitution with U, one step per pivot from the bottom: scale
-        // row i of D, then eliminate it from the rows above (consecutive
-        // threads walk down a column, contiguous in LDS).
-        for (int i = m - 1; i >= 0; --i) {
-            for (int c = tid; c < k; c += kThreads) sD[c * ST + i] /= sMat[i * ST + i];
-            __syncthreads();
-            if (i > 0) {
-                for (int e = tid; e < i * k; e += kThreads) {
-                    const int c = e / i, ii = e % i;
-                    sD[c * ST + ii] -= sMat[ii * ST + i] * sD[c * ST + i];
-                }
-                __syncthreads();
+        // the row that was column j's pivot, divided by it, is row j of D
+        // (columns 0 .. m-1 are not read again)
+#pragma unroll
+        for (int i = 0; i < HR; ++i) {
+            const int row = kParts * i + part;
+            if (row < m) {
+                const int j = __builtin_amdgcn_readlane(place, row);
+                const double d = col[i] / lane_value(pivot, row);
+                if (mine && c >= m) mirror[j] = d;
             }
         }
+        __syncthreads();
     }
     if (writer) a.info[b] = 0;
 
-    // Apply.
     const YT* Y = static_cast<const YT*>(a.Y);
     float* out = a.out + b * a.out_stride;
-    const int total = static_cast<int>(a.qb * a.s);
     const int s = static_cast<int>(a.s);
+    const int total = static_cast<int>(a.qb * a.s);
     const int e0 = static_cast<int>(chunk) * elems_per_block;
     const int e1 = min(total, e0 + elems_per_block);
-    const int passes = m > 0 ? (m + PASS - 1) / PASS : 1;
-    for (int e = e0 + E * tid; e < e1; e += E * kThreads) {
-        const int t = e / s, col = e - t * s;      // E = 4: the four elements share row t
-        for (int pass = 0; pass < passes; ++pass) {
-            const int p0 = pass * PASS;
-            double acc[PASS][E];
+    if (e0 >= e1) return;
+
+    // systematic survivors: (block, E elements) items in one sequence, U per
+    // thread in flight (E == 4: four elements of one row, or of rows that lie
+    // one after another, a block's last group maybe fewer)
+    {
+        constexpr int U = 4;
+        const uint32_t nq = static_cast<uint32_t>(e1 - e0 + E - 1) / E;
+        const uint64_t items = static_cast<uint64_t>(nq) * first_par;
+        const uint32_t dc = kThreads / nq, de = kThreads % nq;
+        uint32_t c = static_cast<uint32_t>(tid) / nq, eq = static_cast<uint32_t>(tid) % nq;
+        for (uint64_t it = tid; it < items; it += kThreads * U) {
+            float v[U][E];
+            int64_t off[U];
+            int left[U], cs[U];          // elements of the item that lie in A
 #pragma unroll
-            for (int bb = 0; bb < PASS; ++bb)
-#pragma unroll
-                for (int v = 0; v < E; ++v) acc[bb][v] = 0.0;
-            for (int c = 0; c < k; ++c) {
-                double y[E];
-                Vec<E, YT>::load(Y + sYoff[c] + e, y);
-                const int w = sS[c];
-                if (pass == 0 && w < k && t < sLim[w]) store_out<E>(a, out, sOoff[w] + static_cast<int64_t>(t) * a.ldo + col, y);
-                const double* dp = sD + c * ST + p0;
-#pragma unroll
-                for (int bb = 0; bb < PASS; bb += 2) {
-                    if (p0 + bb < m) {
-                        const double2 d = *reinterpret_cast<const double2*>(dp + bb);
-#pragma unroll
-                        for (int v = 0; v < E; ++v) {
-                            acc[bb][v] = fma(d.x, y[v], acc[bb][v]);
-                            acc[bb + 1][v] = fma(d.y, y[v], acc[bb + 1][v]);
-                        }
-                    }
+            for (int q = 0; q < U; ++q) {
+                const bool live = it + kThreads * q < items;
+                const uint32_t cc = live ? c : 0;
+                const int e = e0 + E * static_cast<int>(live ? eq : 0);
+                const int w = sm.S[cc];
+                const int t = s == 1 ? e : e / s;
+                load_f32<E, YT>(Y + sm.yoff[cc] + min(e, total - E), v[q]);
+                off[q] = sm.ooff[w] + static_cast<int64_t>(t) * a.ldo + (s == 1 ? 0 : e - t * s);
+                left[q] = live ? (s == 1 ? min(e1, sm.lim[w]) - e : (t < sm.lim[w] ? E : 0)) : 0;
+                cs[q] = cc;
+                c += dc;
+                eq += de;
+                if (eq >= nq) {
+                    eq -= nq;
+                    ++c;
                 }
             }
 #pragma unroll
-            for (int bb = 0; bb < PASS; ++bb) {
-                if (p0 + bb < m) {
-                    const int w = sMiss[p0 + bb];
-                    if (t < sLim[w]) store_out<E>(a, out, sOoff[w] + static_cast<int64_t>(t) * a.ldo + col, acc[bb]);
+            for (int q = 0; q < U; ++q) {
+                if (left[q] >= E)
+                    store_out<E>(a, out, off[q], v[q]);
+                else if (E > 1 && left[q] > 0)       // s == 1: element e of a block is off - ooff
+                    copy_tail(a, out, off[q], Y + sm.yoff[cs[q]] + (off[q] - sm.ooff[sm.S[cs[q]]]), left[q]);
+            }
+        }
+    }
+    if (m == 0) return;
+
+    const int li = lane & 15, lk = lane >> 4;
+    const int steps = (k + 3) / 4;
+    for (int base = e0 + 32 * wv; base < e1; base += 32 * kWaves) {
+        // past the chunk's end: its last element again (a column of the
+        // product depends on that column of Y only, and is not stored)
+        const int el[2] = {min(base + li, e1 - 1), min(base + 16 + li, e1 - 1)};
+        f64x4v acc[RT][2];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = f64x4v{0.0, 0.0, 0.0, 0.0};
+        for (int st = 0; st < steps; st += 8) {
+            YT yv[8][2];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const YT* y = Y + sm.yoff[min(4 * (st + i) + lk, k - 1)];
+                yv[i][0] = y[el[0]];
+                yv[i][1] = y[el[1]];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int c = 4 * (st + i) + lk;
+                const bool ok = c < k;
+                const double y0 = ok ? static_cast<double>(yv[i][0]) : 0.0;
+                const double y1 = ok ? static_cast<double>(yv[i][1]) : 0.0;
+                const double* col = sA + (m + min(c, k - 1)) * LD;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    if (16 * rt < m && st + i < steps) {
+                        const int row = 16 * rt + li;
+                        const double d = col[min(row, m - 1)];
+                        const double dv = ok && row < m ? d : 0.0;
+                        acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y0, acc[rt][0], 0, 0, 0);
+                        acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y1, acc[rt][1], 0, 0, 0);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = base + 16 * h + li;
+            if (e < e1) {
+                const int t = e / s, col = e - t * s;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int bb = 16 * rt + 4 * v + lk;
+                        if (bb < m) {
+                            const int w = sm.miss[bb];
+                            const double val = acc[rt][h][v];
+                            if (t < sm.lim[w])
+                                store_out<1>(a, out, sm.ooff[w] + static_cast<int64_t>(t) * a.ldo + col, &val);
+                        }
+                    }
                 }
             }
         }
@@ -269,12 +359,11 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a, DecodeSe
 // ---------------------------------------------------------------- fast path
 // Codes with at most kFastM missing blocks per set and m + k <= 64: one wave
 // eliminates the m x (m + k) system [G[S_par, M] | -G[S_par, S_sys] | I] in
-// registers (Gauss-Jordan, partial pivoting: the same pivots as the LU above,
+// registers (Gauss-Jordan, partial pivoting: the same pivots as an LU,
 // one column per lane, no workgroup barriers), and the combination of the
 // survivors is one 16-row matrix-core tile:
 //     out[M] (16 x 16 elements) += D (16 x 4 survivors) * Y (4 x 16 elements)
 // on v_mfma_f64_16x16x4f64, with D held in registers for the whole set.
-typedef double f64x4v __attribute__((ext_vector_type(4)));
 
 // Consecutive elements per lane in the combination's loads (E == 4 path);
 // 4 needs 192 registers at k = 48 (2 waves per SIMD) and measured slower.
@@ -316,6 +405,9 @@ __device__ inline int simd_id() {
 // on the other three.  Which wave takes which role changes only the timing.
 // E == 1: wave 0 eliminates while the others start copying; then all four
 // combine.
+// FLAT (E == 4, YBUF, s == ldo == 1): Y and the output at any alignment, blocks
+// of any number of elements; the tails and odd ends cost the others' 80
+// registers (1000 (64,48) sets of 16384 x 8: 185 us against 135).
 // KS: matrix-core K steps (4 survivors each) the kernel is built for, k <= 4 KS;
 // FULL: k == 4 KS (no padding steps).
 // Raw buffer over `bytes` bytes (gfx9 dword-3 value: no stride, no format).
@@ -332,13 +424,13 @@ __device__ inline __amdgpu_buffer_rsrc_t y_buffer(const void* base, uint32_t byt
 // variants with whole survivor groups and buffer-addressed Y up to 12 groups,
 // which then spill one word in the elimination; the others keep the default
 // register budget.
-template <int KS, bool FULL, bool YBUF>
+template <int KS, bool FULL, bool YBUF, bool FLAT>
 constexpr int decode_min_waves() {
-    return FULL && YBUF && KS <= 12 ? 6 : 1;
+    return FULL && YBUF && !FLAT && KS <= 12 ? 6 : 1;
 }
 
-template <int KS, int E, typename YT, bool FULL, bool YBUF>
-__global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) void decode_mfma_kernel(
+template <int KS, int E, typename YT, bool FULL, bool YBUF, bool FLAT>
+__global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF, FLAT>())) void decode_mfma_kernel(
     DecodeArgs args, DecodeSet single, int64_t chunks, int elems_per_block) {
     __shared__ SetMeta sm;
     __shared__ double sD[64 * kFastLd];
@@ -451,9 +543,9 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
     }
 
     // E == 4: the copying wave takes the systematic survivors.  Long chunks go
-    // block by block, U four-element items per lane in flight (a batch past
-    // the block's end re-reads its last item and stores nothing), the block's
-    // addresses in scalar registers.  Chunks of up to 128 such items go as one
+    // block by block, U four-element items per lane in flight (an item past
+    // the block's end re-reads its last elements and stores nothing), the
+    // block's addresses in scalar registers.  Chunks of up to 128 such items go as one
     // sequence of (block, four elements) items: block by block, a chunk of 64
     // elements leaves three quarters of the lanes idle and waits for memory
     // once per block ((25,23), 16 columns: 13.2 us against 5.7).  With dense
@@ -462,10 +554,10 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
     if constexpr (E == 4) {
         if (wv == ew) {
             constexpr int U = sizeof(YT) == 8 ? 4 : 8;
-            const bool dense = a.ldo == a.s;
-            const uint32_t nq = static_cast<uint32_t>(e1 - e0) / 4;
+            const bool dense = FLAT || a.ldo == a.s;
+            const uint32_t nq = static_cast<uint32_t>(e1 - e0 + 3) / 4;
             const uint32_t citems = nq * static_cast<uint32_t>(first_par);   // nq k < 2^31 / 4
-            if (nq == 0) return;
+            if (e0 >= e1) return;
             if (nq > 128) {
                 for (int c = 0; c < first_par; ++c) {
                     const int w = __builtin_amdgcn_readfirstlane(sm.S[c]);
@@ -475,13 +567,15 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
                     for (int e = e0 + 4 * lane; e < elim; e += 1024) {
                         float v[4][4];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) load_f32<4, YT>(yr + min(e + 256 * u, elim - 4), v[u]);
+                        for (int u = 0; u < 4; ++u) load_f32<4, YT, FLAT>(yr + min(e + 256 * u, (FLAT ? total : elim) - 4), v[u]);
 #pragma unroll
                         for (int u = 0; u < 4; ++u) {
                             const int ee = e + 256 * u;
-                            if (ee < elim) {
+                            if (ee + (FLAT ? 4 : 1) <= elim) {
                                 const int64_t off = dense ? ee : static_cast<int64_t>(ee / s) * a.ldo + ee % s;
-                                store_out<4>(a, ob, off, v[u]);
+                                store_out<4, FLAT>(a, ob, off, v[u]);
+                            } else if (FLAT && ee < elim) {
+                                copy_tail(a, ob, ee, yr + ee, elim - ee);
                             }
                         }
                     }
@@ -492,17 +586,18 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
             uint32_t c = static_cast<uint32_t>(lane) / nq, eq = static_cast<uint32_t>(lane) % nq;
             for (uint32_t it = lane; it < citems; it += 64 * U) {
                 float v[U][4];
-                int32_t we[U];         // block of item u, -1 for none, and its element
-                int ee[U];
+                int32_t we[U];         // block of item u, -1 for none, its element and the elements from it on
+                int ee[U], left[FLAT ? U : 1];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const bool live = it + 64 * u < citems;
                     const uint32_t cc = live ? c : 0;
                     const int w = sm.S[cc];
                     const int e = e0 + 4 * static_cast<int>(live ? eq : 0);
-                    load_f32<4, YT>(Y + sm.yoff[cc] + e, v[u]);
+                    load_f32<4, YT, FLAT>(Y + sm.yoff[cc] + (FLAT ? min(e, total - 4) : e), v[u]);
                     ee[u] = e;
                     we[u] = live && e < sm.lim[w] * s ? w : -1;
+                    if constexpr (FLAT) left[u] = min(e1, sm.lim[w]) - e;
                     c += dc;
                     eq += de;
                     if (eq >= nq) {
@@ -512,9 +607,13 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (we[u] >= 0) {
+                    if (we[u] < 0) continue;
+                    if (FLAT && left[FLAT ? u : 0] < 4) {
+                        copy_tail(a, out, sm.ooff[we[u]] + ee[u], Y + static_cast<int64_t>(we[u]) * total + ee[u],
+                                  left[FLAT ? u : 0]);
+                    } else {
                         const int64_t off = dense ? ee[u] : static_cast<int64_t>(ee[u] / s) * a.ldo + ee[u] % s;
-                        store_out<4>(a, out, sm.ooff[we[u]] + off, v[u]);
+                        store_out<4, FLAT>(a, out, sm.ooff[we[u]] + off, v[u]);
                     }
                 }
             }
@@ -543,8 +642,9 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
         // products take the elements in each phase.  The results go through
         // this wave's LDS tile (16 blocks x 16 PE elements, fp64) back into
         // element order, and each lane writes 4 consecutive elements of one
-        // block per 16-byte store.  (E == 4: s % 4 == 0 and Y, out 16-byte
-        // aligned, so the chunk bounds and the total are multiples of 4.)
+        // block per 16-byte store, or fewer at the end of a block (E == 4:
+        // s % 4 == 0, or s == 1 with a dense output, read and written at any
+        // alignment).
         constexpr int PE = kDecodePE;
         constexpr int W = 16 * PE;
         const int ngroups = (e1 - e0 + W - 1) / W;
@@ -564,7 +664,7 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
             obase[h] = out + sm.ooff[w];
             elim[h] = bb < m ? min(e1, sm.lim[w] * s) : 0;   // 0: no block for this lane
         }
-        const bool dense = a.ldo == a.s;
+        const bool dense = FLAT || a.ldo == a.s;
         // YBUF: byte offset of this lane's elements of survivor 4 st + lk (a
         // group's elements past the block's end read the next result or zeros
         // past the buffer; those columns are not stored)
@@ -581,17 +681,34 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
             if constexpr (YBUF) {
                 static_assert(PE == 2, "one 2-element load per survivor");
                 const uint32_t so = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base) * sizeof(YT));
+                auto load = [&](uint32_t add, uint32_t so) __attribute__((always_inline)) {
 #pragma unroll
-                for (int st = 0; st < KS; ++st) {
-                    if constexpr (sizeof(YT) == 8) {
-                        const double2 d = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(yrs, yb[st], so, 0));
-                        yv[st][0] = d.x;
-                        yv[st][1] = d.y;
-                    } else {
-                        const float2 f = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(yrs, yb[st], so, 0));
-                        yv[st][0] = f.x;
-                        yv[st][1] = f.y;
+                    for (int st = 0; st < KS; ++st) {
+                        if constexpr (sizeof(YT) == 8) {
+                            const double2 d = __builtin_bit_cast(
+                                double2, __builtin_amdgcn_raw_buffer_load_b128(yrs, yb[st] + add, so, 0));
+                            yv[st][0] = d.x;
+                            yv[st][1] = d.y;
+                        } else {
+                            const float2 f = __builtin_bit_cast(
+                                float2, __builtin_amdgcn_raw_buffer_load_b64(yrs, yb[st] + add, so, 0));
+                            yv[st][0] = f.x;
+                            yv[st][1] = f.y;
+                        }
                     }
+                };
+                if (FLAT && (total & 1) && base + W > total) {
+                    // an odd block's last element has no second one, at the
+                    // end of Y not even in memory: its lane reads the pair
+                    // before and takes the second (no offset falls below zero:
+                    // lane 0 is the last one only when base > 0)
+                    const bool last = base + PE * li == total - 1;
+                    const uint32_t d = base > 0 ? sizeof(YT) : 0;
+                    load(d - (last ? static_cast<uint32_t>(sizeof(YT)) : 0u), so - d);
+#pragma unroll
+                    for (int st = 0; st < KS; ++st) yv[st][0] = last ? yv[st][1] : yv[st][0];
+                } else {
+                    load(0, so);
                 }
             } else {
                 // a group past the chunk's end reads the block's last PE elements
@@ -630,7 +747,11 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF>())) voi
                     const double v4[4] = {r0.x, r1.x, r0.y, r1.y};
                     // s % 4 == 0: the four share one row; dense rows (ldo == s) need no division
                     const int64_t off = dense ? eg : static_cast<int64_t>(eg / s) * a.ldo + eg % s;
-                    store_out<4>(a, obase[h], off, v4);
+                    if (!FLAT || eg + 4 <= elim[h]) {
+                        store_out<4, FLAT>(a, obase[h], off, v4);
+                    } else {
+                        for (int i = 0; i < elim[h] - eg; ++i) store_out<1>(a, obase[h], off + i, &v4[i]);
+                    }
                 }
             }
         }
@@ -674,7 +795,7 @@ bool fast_path_ok(const DecodeArgs& a) {
     return mmax <= kFastM && a.k + mmax <= 64 && static_cast<int64_t>(a.n) * a.qb * a.s <= 0x7FFFFFFF;
 }
 
-template <int E>
+template <int E, bool FLAT>
 hipError_t launch_fast(const DecodeArgs& a, const DecodeSet& single, hipStream_t st) {
     // About 1024 workgroups when the batch is small: a set is cut into chunks
     // of at least 64 elements (each workgroup repeats the small elimination),
@@ -700,18 +821,18 @@ hipError_t launch_fast(const DecodeArgs& a, const DecodeSet& single, hipStream_t
 #define CODED_FAST_Y(KS, FULL, YB)                                                                             \
     do {                                                                                                       \
         if (a.y_f64)                                                                                           \
-            hipLaunchKernelGGL((decode_mfma_kernel<KS, E, double, FULL, YB>), grid, dim3(kThreads), 0, st, a,  \
+            hipLaunchKernelGGL((decode_mfma_kernel<KS, E, double, FULL, YB, FLAT>), grid, dim3(kThreads), 0, st, a,  \
                                single, chunks, per32);                                                         \
         else                                                                                                   \
-            hipLaunchKernelGGL((decode_mfma_kernel<KS, E, float, FULL, YB>), grid, dim3(kThreads), 0, st, a,   \
+            hipLaunchKernelGGL((decode_mfma_kernel<KS, E, float, FULL, YB, FLAT>), grid, dim3(kThreads), 0, st, a,   \
                                single, chunks, per32);                                                         \
     } while (0)
 #define CODED_FAST_F(KS, FULL)                       \
     do {                                             \
-        if (ybuf)                                    \
+        if (FLAT || ybuf)                            \
             CODED_FAST_Y(KS, FULL, E == 4);          \
         else                                         \
-            CODED_FAST_Y(KS, FULL, false);           \
+            CODED_FAST_Y(KS, FULL, FLAT);            \
     } while (0)
 #define CODED_FAST(KS)                          \
     do {                                        \
@@ -732,36 +853,33 @@ hipError_t launch_fast(const DecodeArgs& a, const DecodeSet& single, hipStream_t
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) % 16) == 0; }
 
-template <int PASS, int E>
-hipError_t launch_pe(const DecodeArgs& a, const DecodeSet& single, int st_rows, hipStream_t st) {
+template <int RT, int E>
+hipError_t launch_wide(const DecodeArgs& a, const DecodeSet& single, int mmax, hipStream_t st) {
+    // About 512 workgroups of at least 64 elements: each repeats the
+    // elimination, which outweighs the rest of a short chunk.
     const int64_t total = a.qb * a.s;
-    // One workgroup per set once the batch fills the chip; a few sets are split
-    // over several workgroups.
-    const int64_t max_chunks = std::max<int64_t>(1, ceil_div(total, static_cast<int64_t>(kThreads) * E));
-    const int64_t want = std::max<int64_t>(1, ceil_div(2048, a.batch));
-    const int64_t chunks = std::min(max_chunks, want);
-    const int64_t per = ceil_div(ceil_div(std::max<int64_t>(total, 1), chunks), E) * E;
+    const int64_t want = std::max<int64_t>(1, ceil_div(512, a.batch));
+    const int64_t per = std::max<int64_t>(64, ceil_div(ceil_div(std::max<int64_t>(total, 1), want), 32) * 32);
+    const int64_t chunks = std::max<int64_t>(1, ceil_div(total, per));
     const int64_t blocks = chunks * a.batch;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-    const size_t shmem = decode_lds_bytes(a.k, st_rows);
+    const int LD = std::max(mmax, 1) | 1;            // odd: columns start in different banks
+    const size_t shmem = static_cast<size_t>(a.k + mmax) * LD * sizeof(double);
+    const dim3 grid(static_cast<unsigned>(blocks));
     if (a.y_f64)
-        hipLaunchKernelGGL((decode_kernel<PASS, E, double>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads),
-                           shmem, st, a, single, chunks, static_cast<int>(per), st_rows);
+        hipLaunchKernelGGL((decode_wide_kernel<RT, E, double>), grid, dim3(kWideThreads), shmem, st, a, single, chunks,
+                           static_cast<int>(per), LD);
     else
-        hipLaunchKernelGGL((decode_kernel<PASS, E, float>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads),
-                           shmem, st, a, single, chunks, static_cast<int>(per), st_rows);
+        hipLaunchKernelGGL((decode_wide_kernel<RT, E, float>), grid, dim3(kWideThreads), shmem, st, a, single, chunks,
+                           static_cast<int>(per), LD);
     return hipGetLastError();
-}
-
-template <int PASS>
-hipError_t launch_p(const DecodeArgs& a, const DecodeSet& single, int st_rows, hipStream_t st) {
-    const bool vec4 = a.s % 4 == 0 && a.ldo % 4 == 0 && aligned16(a.out) && aligned16(a.Y) &&
-                      (a.batch == 1 || a.out_stride % 4 == 0) && (a.c == nullptr || aligned16(a.c));
-    return vec4 ? launch_pe<PASS, 4>(a, single, st_rows, st) : launch_pe<PASS, 1>(a, single, st_rows, st);
 }
 
 }  // namespace
 
+// The bound callers check, k st + st^2 + st doubles (st: mmax rounded up to an
+// even number), is at most 128 doubles short of decode_wide_kernel's
+// (k + mmax) (mmax | 1): 63 KB with the kernel's static LDS at the callers' 56.
 size_t decode_lds_bytes(int k, int mmax) {
     const int st = (std::max(mmax, 1) + 1) / 2 * 2;
     return static_cast<size_t>(k * st + st * st + st) * sizeof(double);
@@ -772,15 +890,30 @@ hipError_t launch_decode(const DecodeArgs& a, const DecodeSet* single, int mmax,
     if (a.qb * a.s > 0x7FFFFFFF) return hipErrorInvalidValue;
     DecodeSet s{};
     if (single) s = *single;
+    const bool vec4 = a.s % 4 == 0 && a.ldo % 4 == 0 && aligned16(a.out) && aligned16(a.Y) &&
+                      (a.batch == 1 || a.out_stride % 4 == 0) && (a.c == nullptr || aligned16(a.c));
+    // Outputs whose rows lie one after another are one column of q s elements,
+    // taken four at a time at any alignment: 1000 (16,12) sets of 65536 x 1
+    // 206 us one by one, 115 so; (32,24), 5000 x 5, 900 sets 85 and 48.  A single
+    // set, bound by latency, spreads better over the waves one by one.
+    DecodeArgs flat = a;
+    flat.qb = a.qb * a.s;
+    flat.q = a.q * a.s;
+    flat.s = flat.ldo = 1;
+    const bool dense = a.ldo == a.s && a.batch > 1 && flat.qb >= 4;
     if (fast_path_ok(a)) {
-        const bool vec4 = a.s % 4 == 0 && a.ldo % 4 == 0 && aligned16(a.out) && aligned16(a.Y) &&
-                          (a.batch == 1 || a.out_stride % 4 == 0) && (a.c == nullptr || aligned16(a.c));
-        return vec4 ? launch_fast<4>(a, s, st) : launch_fast<1>(a, s, st);
+        if (vec4) return launch_fast<4, false>(a, s, st);
+        // read as a raw buffer: see ybuf in launch_fast
+        if (dense && static_cast<int64_t>(a.n) * flat.qb * (a.y_f64 ? 8 : 4) < (int64_t(1) << 31))
+            return launch_fast<4, true>(flat, s, st);
+        return launch_fast<1, false>(a, s, st);
     }
-    const int rows = (std::max(mmax, 1) + 1) / 2 * 2;   // even: D pairs are read 16 bytes at a time
-    if (mmax <= 2) return launch_p<2>(a, s, rows, st);
-    if (mmax <= 4) return launch_p<4>(a, s, rows, st);
-    return launch_p<8>(a, s, rows, st);
+    if (mmax > 64) return hipErrorInvalidValue;      // n <= 128: cannot be
+    const DecodeArgs& w = dense ? flat : a;
+    const bool four = vec4 || dense;
+    if (mmax <= 16) return four ? launch_wide<1, 4>(w, s, mmax, st) : launch_wide<1, 1>(a, s, mmax, st);
+    if (mmax <= 32) return four ? launch_wide<2, 4>(w, s, mmax, st) : launch_wide<2, 1>(a, s, mmax, st);
+    return four ? launch_wide<4, 4>(w, s, mmax, st) : launch_wide<4, 1>(a, s, mmax, st);
 }
 
 }  // namespace coded

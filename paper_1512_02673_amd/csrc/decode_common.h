@@ -17,7 +17,6 @@ struct SetMeta {
     int64_t ooff[kMaxN];       // element offset of block j's first row in out
     int32_t lim[kMaxN];        // rows of block j that lie inside A (the rest is padding)
     int32_t status, m;
-    int32_t pivot;             // of an elimination step in LDS
 };
 
 // Bits below position i of a 128-bit mask.

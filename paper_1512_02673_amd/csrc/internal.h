@@ -103,8 +103,8 @@ struct DecodeArgs {
     const float* c = nullptr;
     double alpha = 1.0, beta = 0.0;
 };
-// LDS bytes of the decode kernel's matrices for k survivors and at most mmax
-// missing blocks; launch_decode sizes its dynamic LDS with it.
+// Size of a decode system of k survivors and at most mmax missing blocks that
+// callers hold against the LDS of one workgroup.
 size_t decode_lds_bytes(int k, int mmax);
 hipError_t launch_decode(const DecodeArgs& a, const DecodeSet* single, int mmax, hipStream_t st);
 

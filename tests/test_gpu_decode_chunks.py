@@ -85,3 +85,37 @@ def test_invalid_sets_in_a_batch(lib, torch, n, k):
     ref = torch.from_numpy(B.astype(np.float32)).cuda()
     for b in range(6):
         assert torch.equal(out[b], ref if b in (0, 3, 5) else torch.full_like(ref, -1.0))
+
+
+# Outputs whose rows lie one after another, taken four at a time at any
+# alignment: blocks of 1 to 3 elements past a group, odd totals (whose last pair
+# would start inside Y and end past it), several chunks, a last block with no
+# and with few rows in A.
+@pytest.mark.parametrize("n,k,q,s", [(16, 12, 12 * 5, 1), (16, 12, 12 * 7 - 1, 1), (25, 23, 23 * 65 - 22, 1),
+                                     (64, 48, 48 * 131, 1), (64, 48, 48 * 43 - 5, 3), (20, 16, 16 * 1027 - 3, 1),
+                                     (32, 24, 24 * 37 - 23, 5), (10, 8, 9, 6), (44, 33, 33 * 9 - 1, 7)])
+@pytest.mark.parametrize("batch,shift,f32", [(2, 0, False), (2, 1, True), (7, 3, False), (1100, 2, False)])
+def test_decode_flat(lib, torch, n, k, q, s, batch, shift, f32):
+    if batch > 1000 and q * s * batch > 3e7:
+        pytest.skip("batch too large for this shape")
+    code, B, sets, Y, _ = _case(lib, torch, n, k, q, s, batch, 0)
+    if f32:
+        # integer parity rows keep the results whole numbers below 2^24
+        P = synth.integer_parity_matrix(n, k, 5)
+        keep = [np.sort(S) for S in sets]
+        sets = np.stack([S if np.linalg.matrix_rank(np.vstack([np.eye(k), P])[S]) == k else
+                         np.arange(k, dtype=np.int32) for S in keep])
+        code = lib.Code.systematic(P, 2)
+        Bb = np.zeros((k * -(-q // k), s))
+        Bb[:q] = B
+        Bb = Bb.reshape(k, -1)
+        Y = torch.from_numpy(np.concatenate([Bb, np.asarray(P, np.float64) @ Bb]).reshape(n, -1, s)).cuda().float()
+    whole = torch.full((batch * q * s + shift + 8,), -1.0, device="cuda")
+    view = whole[shift:shift + batch * q * s].view(batch, q, s)
+    info = torch.full((batch,), 9, dtype=torch.int32, device="cuda")
+    lib.coded_decode_batched(code, torch.from_numpy(sets).cuda(), Y, q, view, info)
+    torch.cuda.synchronize()
+    assert torch.all(info == 0)
+    ref = torch.from_numpy(B.astype(np.float32)).cuda()
+    assert torch.equal(view, ref.expand(batch, q, s))
+    assert torch.all(whole[:shift] == -1.0) and torch.all(whole[shift + batch * q * s:] == -1.0)

@@ -1,0 +1,110 @@
+"""Decodes of codes past the register elimination: one to 54 missing blocks, row
+and column tiles with remainders, both Y types, strided and unaligned outputs, a
+singular system.
+
+As in the chunk tests the block products are integers from 1 to 7 and the solve
+runs in fp64, so a result off by the condition number (under 1e6 here) times a
+few 2^-53 rounds to the integer in fp32.  With fp32 Y the parity results are
+rounded, 2^-24 of up to 7 k 4 in size, times the condition number: those
+compare within that."""
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_helpers import torch_mod
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    t = torch_mod()
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+def _sets(n, k, m, P, batch, seed):
+    """Survivor sets with m missing blocks, the best conditioned of a few draws, in any order."""
+    g = np.random.default_rng(seed)
+    found = []
+    for _ in range(4 * batch):
+        miss = np.sort(g.choice(k, m, replace=False))
+        par = np.sort(g.choice(n - k, m, replace=False))
+        S = np.concatenate([np.setdiff1d(np.arange(k), miss), k + par]).astype(np.int32)
+        cond = np.linalg.cond(P[par][:, miss].astype(np.float64)) if m else 1.0
+        g.shuffle(S)
+        found.append((cond, len(found), S))
+    found.sort()
+    return np.stack([S for _, _, S in found[:batch]]), found[batch - 1][0]
+
+
+def _results(P, k, q, s, seed):
+    g = np.random.default_rng(seed)
+    qb = -(-q // k)
+    B = np.zeros((k * qb, s))
+    B[:q] = g.integers(1, 8, (q, s))
+    Bb = B.reshape(k, qb * s)
+    return B[:q], np.concatenate([Bb, P.astype(np.float64) @ Bb]).reshape(-1, qb, s)
+
+
+# (n, k, m): row tiles of 16, 32 and 64 with and without remainders, an empty
+# second half of the rows, the widest accepted system, more than 64 survivors
+CODES = [(128, 127, 1), (66, 50, 16), (66, 50, 0), (34, 17, 17), (96, 64, 31), (128, 96, 32), (66, 33, 33), (100, 50, 48),
+         (128, 74, 54)]
+
+
+@pytest.mark.parametrize("n,k,m", CODES)
+@pytest.mark.parametrize("rows,s,pad", [(1, 1, 0), (16, 2, 1), (33, 1, 0), (11, 4, 4), (300, 4, 0)])
+@pytest.mark.parametrize("batch", [1, 5])
+def test_decode_wide(lib, torch, n, k, m, rows, s, pad, batch):
+    P = synth.parity_matrix(n, k, 6)
+    sets, cond = _sets(n, k, m, P, batch, n + m)
+    assert cond < 1e6
+    q = max(1, k * rows - (rows > 1) * 3)
+    B, Y = _results(P, k, q, s, rows)
+    code = lib.Code.systematic(P, 2)
+    ref = torch.from_numpy(B.astype(np.float32)).cuda()
+    for dt in (torch.float64, torch.float32):
+        dY = torch.from_numpy(Y).cuda().to(dt)
+        out = torch.full((batch, q, s + pad), -1.0, device="cuda")
+        info = torch.full((batch,), 9, dtype=torch.int32, device="cuda")
+        lib.coded_decode_batched(code, torch.from_numpy(sets).cuda(), dY, q, out[:, :, :s], info)
+        one = torch.full((q, s + pad), -1.0, device="cuda")
+        oinfo = torch.full((1,), 9, dtype=torch.int32, device="cuda")
+        lib.coded_decode(code, sets[-1], dY, q, one[:, :s], oinfo)
+        torch.cuda.synchronize()
+        assert torch.all(info == 0) and int(oinfo) == 0
+        assert torch.equal(one, out[-1])              # alone as in a batch
+        assert torch.all(out[:, :, s:] == -1.0)
+        got = out[:, :, :s]
+        if dt == torch.float64:
+            assert torch.equal(got, ref.expand(batch, q, s))
+        else:
+            # every rounded result is off by at most 2^-24 of 28 k; the solve
+            # multiplies the 2-norm of k of them by the condition number over
+            # the smallest column norm, at least 1/2 here
+            assert float((got - ref).abs().max()) <= 2.0 ** -24 * 28 * k * 2 * cond * np.sqrt(k)
+
+
+@pytest.mark.parametrize("n,k,m", [(96, 64, 20), (128, 96, 32)])
+def test_singular_wide_set(lib, torch, n, k, m):
+    """Two equal parity rows: a zero pivot, reported, and nothing written; its neighbours in the batch decode."""
+    P = synth.integer_parity_matrix(n, k, 3).astype(np.float64)
+    P[4] = P[3]
+    g = np.random.default_rng(1)
+    miss = np.sort(g.choice(k, m, replace=False))
+    bad = np.concatenate([np.setdiff1d(np.arange(k), miss), k + np.arange(m)]).astype(np.int32)
+    good = np.concatenate([np.setdiff1d(np.arange(k), miss[:1]), [k]]).astype(np.int32)
+    P[0, miss[0]] = 2.0
+    q, s = 7 * k, 2
+    B, Y = _results(P, k, q, s, 2)
+    out = torch.full((3, q, s), -1.0, device="cuda")
+    info = torch.zeros(3, dtype=torch.int32, device="cuda")
+    sets = torch.from_numpy(np.stack([good, bad, good])).cuda()
+    lib.coded_decode_batched(lib.Code.systematic(P, 2), sets, torch.from_numpy(Y).cuda(), q, out, info)
+    torch.cuda.synchronize()
+    assert info[0] == 0 and info[2] == 0 and k - m < int(info[1]) <= k
+    ref = torch.from_numpy(B.astype(np.float32)).cuda()
+    assert torch.equal(out[0], ref) and torch.equal(out[2], ref)
+    assert torch.all(out[1] == -1.0)
