@@ -7,8 +7,9 @@
 // by HBM bandwidth, not arithmetic (about 2 flops per byte, far below the
 // matrix cores' ridge): each thread owns a short vector of columns of one
 // block row t, walks the k blocks j with kBatch loads in flight, and keeps up
-// to kGroup parity accumulators in registers; the sum runs over j in order.  Parity rows beyond kGroup are
-// handled by further groups (grid.y), each re-reading A.
+// to kGroup parity accumulators in registers; the sum runs over j in order.
+// Parity rows beyond kGroup are handled by further groups, each re-reading A
+// while the others of its rows do.
 //
 // Rows start at any element boundary and have any length: a thread's vector
 // (VEC columns) that would pass the row's end is moved back to end with it, so
@@ -45,20 +46,33 @@ int row_threads(int64_t r, int vec) {
     return v < kThreads ? static_cast<int>(v) : kThreads;
 }
 
+// The workgroup's row index (in units of the rows it takes) and first parity
+// row.  Workgroups go to the 8 XCDs in turn, so the groups of parity rows that
+// read the same rows of A sit 8 apart: they run on one XCD at about the same
+// time, and A comes from HBM once ((64,48), 16 parity rows in two groups, on
+// 40000 x 4000: 349 us with the groups one after the other, 241 here; 60000 x
+// 4097 bf16 275).
+__device__ inline void row_and_group(int groups, int64_t& t, int& p0) {
+    const uint32_t b = blockIdx.x, rest = b >> 3, g = static_cast<uint32_t>(groups);
+    t = groups > 1 ? static_cast<int64_t>(rest / g) * 8 + (b & 7) : b;
+    p0 = groups > 1 ? static_cast<int>(rest % g) * kGroup : 0;
+}
+
 // One thread: VEC consecutive columns of block row t, parity rows
 // [p0, p0 + np) with np <= kGroup.
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int64_t col_chunks, int width) {
+__global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int groups, int width) {
     __shared__ double sP[kGroup * kMaxN];
-    int64_t t = blockIdx.x;
+    int64_t t;
+    int p0;
+    row_and_group(groups, t, p0);
     int lane = threadIdx.x;
     if (width < kThreads) {               // several rows: this thread's row and place in it
         const int per = kThreads / width, row = lane / width;
         t = t * per + row;
         lane = row < per ? lane - row * width : kThreads;
     }
-    const int64_t chunk = blockIdx.y % col_chunks;
-    const int p0 = static_cast<int>(blockIdx.y / col_chunks) * kGroup;
+    const int64_t chunk = blockIdx.y;
     const int npar = a.n - a.k;
     const int np = min(kGroup, npar - p0);
     const int k = a.k;
@@ -154,17 +168,18 @@ __global__ __launch_bounds__(kThreads) void encode_f32_kernel(EncodeArgs a, int6
 // bf16: products of two bf16 values are exact in fp32; the k-term sum is
 // accumulated in fp32 and split into bf16 hi + lo.
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int64_t col_chunks, int width) {
+__global__ __launch_bounds__(kThreads) void encode_bf16_kernel(EncodeArgs a, int groups, int width) {
     __shared__ float sP[kGroup * kMaxN];
-    int64_t t = blockIdx.x;
+    int64_t t;
+    int p0;
+    row_and_group(groups, t, p0);
     int lane = threadIdx.x;
     if (width < kThreads) {               // several rows: this thread's row and place in it
         const int per = kThreads / width, row = lane / width;
         t = t * per + row;
         lane = row < per ? lane - row * width : kThreads;
     }
-    const int64_t chunk = blockIdx.y % col_chunks;
-    const int p0 = static_cast<int>(blockIdx.y / col_chunks) * kGroup;
+    const int64_t chunk = blockIdx.y;
     const int npar = a.n - a.k;
     const int np = min(kGroup, npar - p0);
     const int k = a.k;
@@ -260,11 +275,13 @@ hipError_t launch_encode_f32(const EncodeArgs& a, hipStream_t st) {
     if (chunks * groups > 65535) return hipErrorInvalidConfiguration;
     const int width = row_threads(a.r, V);
     const int64_t rows = ceil_div(a.qb, kThreads / width);
-    dim3 grid(static_cast<unsigned>(rows), static_cast<unsigned>(chunks * groups));
+    const int64_t blocks = groups > 1 ? ceil_div(rows, 8) * 8 * groups : rows;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(chunks));
     if (vec)
-        hipLaunchKernelGGL(encode_f32_kernel<4>, grid, dim3(kThreads), 0, st, a, chunks, width);
+        hipLaunchKernelGGL(encode_f32_kernel<4>, grid, dim3(kThreads), 0, st, a, groups, width);
     else
-        hipLaunchKernelGGL(encode_f32_kernel<1>, grid, dim3(kThreads), 0, st, a, chunks, width);
+        hipLaunchKernelGGL(encode_f32_kernel<1>, grid, dim3(kThreads), 0, st, a, groups, width);
     return hipGetLastError();
 }
 
@@ -278,11 +295,13 @@ hipError_t launch_encode_bf16(const EncodeArgs& a, hipStream_t st) {
     if (chunks * groups > 65535) return hipErrorInvalidConfiguration;
     const int width = row_threads(a.r, V);
     const int64_t rows = ceil_div(a.qb, kThreads / width);
-    dim3 grid(static_cast<unsigned>(rows), static_cast<unsigned>(chunks * groups));
+    const int64_t blocks = groups > 1 ? ceil_div(rows, 8) * 8 * groups : rows;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(chunks));
     if (vec)
-        hipLaunchKernelGGL(encode_bf16_kernel<8>, grid, dim3(kThreads), 0, st, a, chunks, width);
+        hipLaunchKernelGGL(encode_bf16_kernel<8>, grid, dim3(kThreads), 0, st, a, groups, width);
     else
-        hipLaunchKernelGGL(encode_bf16_kernel<1>, grid, dim3(kThreads), 0, st, a, chunks, width);
+        hipLaunchKernelGGL(encode_bf16_kernel<1>, grid, dim3(kThreads), 0, st, a, groups, width);
     return hipGetLastError();
 }
 

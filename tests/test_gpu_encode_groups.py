@@ -1,0 +1,41 @@
+"""Encodes with more than eight parity rows: groups of parity rows over the same
+block rows, with row counts that are no multiple of the eight they are dealt in.
+
+Integer inputs keep every sum exact, so the planes equal the oracle's."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import coded as oc
+from tests.gpu_helpers import device_tensor, make_inputs, torch_mod
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    t = torch_mod()
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+# two groups (one partial) and more; one, seven, eight, nine and seventeen block rows; several rows per
+# workgroup, one, and several column chunks
+@pytest.mark.parametrize("n,k,q,r", [(12, 3, 3, 40), (19, 10, 70, 1024), (64, 48, 48 * 8, 2050), (30, 7, 7 * 9 - 2, 3000),
+                                     (128, 64, 64 * 17 - 5, 33), (40, 4, 4 * 131, 9), (20, 2, 34, 3)])
+def test_encode_groups(lib, torch, dtype, n, k, q, r):
+    P, A, _ = make_inputs(n, k, q, r, 1, 17, dtype, integer=True)
+    code = lib.Code.systematic(P, 2)
+    dA = device_tensor(A, dtype)
+    par = lib.alloc_parity(code, q, r, dA.dtype)
+    par.fill_(-3.0)
+    lib.coded_encode(code, dA, par)
+    torch.cuda.synchronize()
+    ref = oc.encode(oc.systematic_generator(P), oc.pad_and_split(A, k))[k:]
+    got = par.float().cpu().numpy().astype(np.float64)
+    if dtype == "f32":
+        assert np.array_equal(got[0], ref) and np.all(got[1] == 0)
+    else:
+        assert np.array_equal(got[0] + got[1], ref)     # whole numbers below 2^16: 8 + 8 bits hold them
