@@ -112,3 +112,36 @@ def test_shuffle_nothing_to_send(lib, torch):
         assert np.array_equal(tb["enc_off"], p.enc_off) and np.array_equal(tb["next_assign"], p.new_assign)
         st.commit()
         ref = sh.commit(ref, p)
+
+
+@pytest.mark.parametrize("r,pad", [(65, 0), (67, 1), (130, 2), (255, 0), (257, 3), (514, 1), (64, 1), (3, 0)])
+def test_shuffle_rows_at_any_boundary(lib, torch, r, pad):
+    """Rows of any length and stride, the data and both outputs one element off
+    a 16-byte boundary; nothing beside the rows is written."""
+    n, q, cache = 6, 300, 100
+    wide = synth.gaussian((q, r + pad), 54, synth.STREAM_A)
+    A = wide[:, :r]
+
+    def place(rows, fill):
+        """A rows x r view with row stride r + pad, one element into its buffer."""
+        buf = torch.full((rows * (r + pad) + 9,), fill, dtype=torch.float32, device="cuda")
+        return buf, buf[1:1 + rows * (r + pad)].view(rows, r + pad)[:, :r]
+
+    _, dA = place(q, 0.0)
+    dA.copy_(torch.from_numpy(np.ascontiguousarray(A)))
+    st = lib.Shuffle(n, q, cache, 7)
+    coded_rows, terms = st.plan()
+    tb = st.tables()
+    p = sh.plan(sh.initial_state(n, q, cache, 7))
+    dev = {k: torch.from_numpy(tb[k]).cuda() for k in ("enc_off", "enc_rows", "term_msg")}
+    mbuf, M = place(coded_rows, -9.0)
+    obuf, out = place(terms, -9.0)
+    lib.coded_shuffle_encode(dA, dev["enc_off"], dev["enc_rows"], M)
+    lib.coded_shuffle_decode(dA, M, dev["enc_off"], dev["enc_rows"], dev["term_msg"], out)
+    torch.cuda.synchronize()
+    M_ref = sh.encode(np.ascontiguousarray(A), p)
+    assert np.array_equal(M.cpu().numpy(), M_ref)
+    assert np.array_equal(out.cpu().numpy(), sh.decode(np.ascontiguousarray(A), M_ref, p))
+    for buf, view in ((mbuf, M), (obuf, out)):
+        view.fill_(-9.0)
+        assert torch.all(buf == -9.0)
