@@ -3,6 +3,7 @@
 // that forms the decoding matrix D (Sec. III-A, dec(indices, results)).
 #pragma once
 #include "internal.h"
+#include "survivor_mask.h"
 
 namespace coded {
 namespace {
@@ -18,13 +19,6 @@ struct SetMeta {
     int32_t lim[kMaxN];        // rows of block j that lie inside A (the rest is padding)
     int32_t status, m;
 };
-
-// Bits below position i of a 128-bit mask.
-__device__ inline int bits_below(uint64_t m0, uint64_t m1, int i) {
-    const uint64_t b0 = i >= 64 ? ~uint64_t{0} : (uint64_t{1} << i) - 1;
-    const uint64_t b1 = i > 64 ? (uint64_t{1} << (i - 64)) - 1 : 0;
-    return __popcll(m0 & b0) + __popcll(m1 & b1);
-}
 
 // Reads set b as a bit mask of the survivors (a single set comes as one),
 // validates it (range, repeats) and fills the bookkeeping: a worker's place

@@ -49,9 +49,10 @@ def _results(P, k, q, s, seed):
 
 
 # (n, k, m): row tiles of 16, 32 and 64 with and without remainders, an empty
-# second half of the rows, the widest accepted system, more than 64 survivors
-CODES = [(128, 127, 1), (66, 50, 16), (66, 50, 0), (34, 17, 17), (96, 64, 31), (128, 96, 32), (66, 33, 33), (100, 50, 48),
-         (128, 74, 54)]
+# second half of the rows, the widest accepted system, more than 64 survivors,
+# codes without parity workers (k = 128 takes the whole survivor mask)
+CODES = [(128, 128, 0), (65, 65, 0), (127, 127, 0), (128, 127, 1), (66, 50, 16), (66, 50, 0), (34, 17, 17),
+         (96, 64, 31), (128, 96, 32), (66, 33, 33), (100, 50, 48), (128, 74, 54)]
 
 
 @pytest.mark.parametrize("n,k,m", CODES)
@@ -85,6 +86,24 @@ def test_decode_wide(lib, torch, n, k, m, rows, s, pad, batch):
             # multiplies the 2-norm of k of them by the condition number over
             # the smallest column norm, at least 1/2 here
             assert float((got - ref).abs().max()) <= 2.0 ** -24 * 28 * k * 2 * cond * np.sqrt(k)
+
+
+@pytest.mark.parametrize("n", [65, 128])
+@pytest.mark.parametrize("s", [1, 3])
+def test_product_without_parity_workers(lib, torch, n, s):
+    """coded_matmul with k = n > 64: every worker survives, and the blocks are copied."""
+    q, r = 2 * n + 1, 24
+    A = torch.from_numpy(synth.integers((q, r), 3, synth.STREAM_A).astype(np.float32)).cuda()
+    X = torch.from_numpy(synth.integers((r, s), 3, synth.STREAM_X).astype(np.float32)).cuda()
+    ref = A.double() @ X.double()
+    X = X.view(-1) if s == 1 else X
+    code = lib.Code.systematic(np.zeros((0, n)), 2)
+    parity = lib.alloc_parity(code, q, r, torch.float32)
+    out = torch.full((q, s) if s > 1 else (q,), -1.0, device="cuda")
+    info = torch.full((1,), 9, dtype=torch.int32, device="cuda")
+    lib.coded_matmul(code, A, parity, X, out, lib.matmul_workspace(code, A, X), info, 2, 0)
+    torch.cuda.synchronize()
+    assert int(info) == 0 and torch.equal(out.view(q, s).double(), ref)
 
 
 @pytest.mark.parametrize("n,k,m", [(96, 64, 20), (128, 96, 32)])

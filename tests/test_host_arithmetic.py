@@ -1,0 +1,37 @@
+"""Index and size arithmetic that kernels and launches share, compiled for the host
+from the library's own headers with the undefined-behaviour sanitizer and run."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1512_02673_amd", "csrc")
+
+
+def run_host(tmp_path, source):
+    """Compile a host program against csrc/ and run it; a failed check or undefined behaviour ends it with an error."""
+    src, exe = tmp_path / "check.cpp", tmp_path / "check"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <cstdlib>\n"
+                   "#define CHECK(c, ...) do { if (!(c)) { std::printf(__VA_ARGS__); std::exit(1); } } while (0)\n" + source)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", f"-I{CSRC}",
+                    str(src), "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_bits_below_every_position(tmp_path):
+    """Every position of 0 .. 128 (128: the whole mask, the place of k in a code of 128 blocks)."""
+    run_host(tmp_path, r"""
+#include "survivor_mask.h"
+int main() {
+    const uint64_t masks[][2] = {{~0ull, ~0ull}, {0, 0}, {1, 1ull << 63}, {~0ull, 1}, {0x8000000000000001ull, ~0ull},
+                                 {0x0123456789abcdefull, 0xfedcba9876543210ull}};
+    for (const auto& m : masks)
+        for (int i = 0; i <= 128; ++i) {
+            int want = 0;
+            for (int b = 0; b < i; ++b) want += (m[b / 64] >> (b % 64)) & 1;
+            const int got = coded::bits_below(m[0], m[1], i);
+            CHECK(got == want, "bits below %d: %d, not %d\n", i, got, want);
+        }
+}
+""")
