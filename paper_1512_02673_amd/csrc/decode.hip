@@ -26,6 +26,7 @@
 // otherwise, lanes on consecutive elements.
 #include "internal.h"
 #include "decode_common.h"
+#include "launch_rules.h"
 
 namespace coded {
 namespace {
@@ -145,7 +146,7 @@ constexpr int kWideThreads = 512;
 
 template <int RT, int E, typename YT>
 __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a, DecodeSet single, int64_t chunks,
-                                                               int elems_per_block, int LD) {
+                                                                   uint32_t elems_per_block, int LD) {
     __shared__ SetMeta sm;
     extern __shared__ __align__(16) double sA[];     // column c at sA[c * LD], LD odd, rows 0 .. m-1
     constexpr int kThreads = kWideThreads, kWaves = kThreads / 64;
@@ -249,18 +250,19 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a,
 
     const YT* Y = static_cast<const YT*>(a.Y);
     float* out = a.out + b * a.out_stride;
-    const int s = static_cast<int>(a.s);
-    const int total = static_cast<int>(a.qb * a.s);
-    const int e0 = static_cast<int>(chunk) * elems_per_block;
-    const int e1 = min(total, e0 + elems_per_block);
-    if (e0 >= e1) return;
+    // elements below 2^31, positions past a chunk's end below 2^32
+    const uint32_t s = static_cast<uint32_t>(a.s);
+    const uint32_t total = static_cast<uint32_t>(a.qb * a.s);
+    const uint32_t e0 = static_cast<uint32_t>(chunk) * elems_per_block;
+    if (e0 >= total) return;
+    const uint32_t e1 = chunk_end(e0, elems_per_block, total);
 
     // systematic survivors: (block, E elements) items in one sequence, U per
     // thread in flight (E == 4: four elements of one row, or of rows that lie
     // one after another, a block's last group maybe fewer)
     {
         constexpr int U = 4;
-        const uint32_t nq = static_cast<uint32_t>(e1 - e0 + E - 1) / E;
+        const uint32_t nq = (e1 - e0 + E - 1) / E;
         const uint64_t items = static_cast<uint64_t>(nq) * first_par;
         const uint32_t dc = kThreads / nq, de = kThreads % nq;
         uint32_t c = static_cast<uint32_t>(tid) / nq, eq = static_cast<uint32_t>(tid) % nq;
@@ -272,12 +274,12 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a,
             for (int q = 0; q < U; ++q) {
                 const bool live = it + kThreads * q < items;
                 const uint32_t cc = live ? c : 0;
-                const int e = e0 + E * static_cast<int>(live ? eq : 0);
+                const uint32_t e = e0 + E * (live ? eq : 0);
                 const int w = sm.S[cc];
-                const int t = s == 1 ? e : e / s;
+                const uint32_t t = s == 1 ? e : e / s, lim = static_cast<uint32_t>(sm.lim[w]);
                 load_f32<E, YT>(Y + sm.yoff[cc] + min(e, total - E), v[q]);
                 off[q] = sm.ooff[w] + static_cast<int64_t>(t) * a.ldo + (s == 1 ? 0 : e - t * s);
-                left[q] = live ? (s == 1 ? min(e1, sm.lim[w]) - e : (t < sm.lim[w] ? E : 0)) : 0;
+                left[q] = live ? (s == 1 ? static_cast<int>(min(e1, lim) - e) : (t < lim ? E : 0)) : 0;
                 cs[q] = cc;
                 c += dc;
                 eq += de;
@@ -299,10 +301,10 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a,
 
     const int li = lane & 15, lk = lane >> 4;
     const int steps = (k + 3) / 4;
-    for (int base = e0 + 32 * wv; base < e1; base += 32 * kWaves) {
+    for (uint32_t base = e0 + 32 * wv; base < e1; base += 32 * kWaves) {
         // past the chunk's end: its last element again (a column of the
         // product depends on that column of Y only, and is not stored)
-        const int el[2] = {min(base + li, e1 - 1), min(base + 16 + li, e1 - 1)};
+        const uint32_t el[2] = {min(base + li, e1 - 1), min(base + 16 + li, e1 - 1)};
         f64x4v acc[RT][2];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = f64x4v{0.0, 0.0, 0.0, 0.0};
@@ -335,9 +337,9 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a,
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int e = base + 16 * h + li;
+            const uint32_t e = base + 16 * h + li;
             if (e < e1) {
-                const int t = e / s, col = e - t * s;
+                const uint32_t t = e / s, col = e - t * s;
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
 #pragma unroll
@@ -346,7 +348,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a,
                         if (bb < m) {
                             const int w = sm.miss[bb];
                             const double val = acc[rt][h][v];
-                            if (t < sm.lim[w])
+                            if (t < static_cast<uint32_t>(sm.lim[w]))
                                 store_out<1>(a, out, sm.ooff[w] + static_cast<int64_t>(t) * a.ldo + col, &val);
                         }
                     }
@@ -789,10 +791,13 @@ __global__ __launch_bounds__(kThreads, (decode_min_waves<KS, FULL, YBUF, FLAT>()
 }
 
 // The fast path takes codes (not sets) by their largest possible m, so a set
-// decodes with the same arithmetic alone or in a batch.
+// decodes with the same arithmetic alone or in a batch.  Its positions are
+// signed 32-bit, some of them past a block's end: blocks of up to 2^30
+// elements (one worker alone may have twice that).
 bool fast_path_ok(const DecodeArgs& a) {
     const int mmax = std::min(a.k, a.n - a.k);
-    return mmax <= kFastM && a.k + mmax <= 64 && static_cast<int64_t>(a.n) * a.qb * a.s <= 0x7FFFFFFF;
+    return mmax <= kFastM && a.k + mmax <= 64 && static_cast<int64_t>(a.n) * a.qb * a.s <= 0x7FFFFFFF &&
+           a.qb * a.s <= (int64_t(1) << 30);
 }
 
 template <int E, bool FLAT>
@@ -808,14 +813,12 @@ hipError_t launch_fast(const DecodeArgs& a, const DecodeSet& single, hipStream_t
     // 64: 28.7 and 26.1).
     const int64_t total = a.qb * a.s;
     const int64_t target = a.batch > 1 && std::min(a.k, a.n - a.k) > 4 ? 512 : 1024;
-    const int64_t want = std::max<int64_t>(1, ceil_div(target, a.batch));
-    const int64_t per = std::max<int64_t>(64, ceil_div(ceil_div(std::max<int64_t>(total, 1), want), 16) * 16);
-    const int64_t chunks = std::max<int64_t>(1, ceil_div(total, per));
-    const int64_t blocks = chunks * a.batch;
+    const Chunks cut = split_chunks(total, ceil_div(target, a.batch), 16);
+    const int64_t chunks = cut.count, blocks = chunks * a.batch;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
     const int ksteps = (a.k + 3) / 4;
     const dim3 grid(static_cast<unsigned>(blocks));
-    const int per32 = static_cast<int>(per);
+    const int per32 = static_cast<int>(cut.per);
     // Y read as a raw buffer (E == 4) when its byte offsets fit in 31 bits
     const bool ybuf = E == 4 && static_cast<int64_t>(a.n) * total * (a.y_f64 ? 8 : 4) < (int64_t(1) << 31);
 #define CODED_FAST_Y(KS, FULL, YB)                                                                             \
@@ -858,20 +861,18 @@ hipError_t launch_wide(const DecodeArgs& a, const DecodeSet& single, int mmax, h
     // About 512 workgroups of at least 64 elements: each repeats the
     // elimination, which outweighs the rest of a short chunk.
     const int64_t total = a.qb * a.s;
-    const int64_t want = std::max<int64_t>(1, ceil_div(512, a.batch));
-    const int64_t per = std::max<int64_t>(64, ceil_div(ceil_div(std::max<int64_t>(total, 1), want), 32) * 32);
-    const int64_t chunks = std::max<int64_t>(1, ceil_div(total, per));
-    const int64_t blocks = chunks * a.batch;
+    const Chunks cut = split_chunks(total, ceil_div(512, a.batch), 32);
+    const int64_t blocks = cut.count * a.batch;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
     const int LD = std::max(mmax, 1) | 1;            // odd: columns start in different banks
     const size_t shmem = static_cast<size_t>(a.k + mmax) * LD * sizeof(double);
     const dim3 grid(static_cast<unsigned>(blocks));
     if (a.y_f64)
-        hipLaunchKernelGGL((decode_wide_kernel<RT, E, double>), grid, dim3(kWideThreads), shmem, st, a, single, chunks,
-                           static_cast<int>(per), LD);
+        hipLaunchKernelGGL((decode_wide_kernel<RT, E, double>), grid, dim3(kWideThreads), shmem, st, a, single, cut.count,
+                           static_cast<uint32_t>(cut.per), LD);
     else
-        hipLaunchKernelGGL((decode_wide_kernel<RT, E, float>), grid, dim3(kWideThreads), shmem, st, a, single, chunks,
-                           static_cast<int>(per), LD);
+        hipLaunchKernelGGL((decode_wide_kernel<RT, E, float>), grid, dim3(kWideThreads), shmem, st, a, single, cut.count,
+                           static_cast<uint32_t>(cut.per), LD);
     return hipGetLastError();
 }
 

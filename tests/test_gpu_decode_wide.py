@@ -106,6 +106,28 @@ def test_product_without_parity_workers(lib, torch, n, s):
     assert int(info) == 0 and torch.equal(out.view(q, s).double(), ref)
 
 
+# Blocks of 2^31 - 1 elements (the longest accepted): a copied block and a
+# recovered one, single elements and groups of four.
+@pytest.mark.parametrize("n,q,s", [(1, 2 ** 31 - 1, 1), (1, 2 ** 29 - 1, 4), (2, 2 ** 31 - 1, 1), (2, 2 ** 29 - 1, 4)])
+def test_decode_of_the_longest_blocks(lib, torch, n, q, s):
+    code = lib.Code.systematic(np.ones((n - 1, 1)), 2)
+    Y = torch.empty((n, q, s), dtype=torch.float32, device="cuda")
+    period = (1 << 20) + 7                               # values 0 .. 2^20 + 6, no two chunks alike
+    pattern = torch.arange(period, device="cuda", dtype=torch.float32)
+    flat = Y[n - 1].view(-1)
+    for i in range(0, q * s, period):
+        part = flat[i:i + period]
+        part.copy_(pattern[:part.numel()])
+    if n == 2:
+        Y[0].fill_(-2.0)
+    out = torch.full((q, s), -1.0, device="cuda")
+    info = torch.full((1,), 9, dtype=torch.int32, device="cuda")
+    lib.coded_decode(code, [n - 1], Y, q, out, info)
+    torch.cuda.synchronize()
+    assert int(info) == 0
+    assert torch.equal(out, Y[n - 1])
+
+
 @pytest.mark.parametrize("n,k,m", [(96, 64, 20), (128, 96, 32)])
 def test_singular_wide_set(lib, torch, n, k, m):
     """Two equal parity rows: a zero pivot, reported, and nothing written; its neighbours in the batch decode."""

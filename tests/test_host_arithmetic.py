@@ -35,3 +35,30 @@ int main() {
         }
 }
 """)
+
+
+def test_chunks_cover_their_range(tmp_path):
+    """Chunks meet end to end and end with the range, up to the longest one (2^31 - 1
+    elements); the tile loops' steps of 256 past an end stay in 32 bits."""
+    run_host(tmp_path, r"""
+#include "launch_rules.h"
+int main() {
+    const int64_t totals[] = {1, 63, 64, 65, 4096, 32768 + 5, (1ll << 30) + 1, (1ll << 31) - 16384, (1ll << 31) - 2, (1ll << 31) - 1};
+    const int64_t wants[] = {1, 2, 500, 512, 1024};
+    const int64_t units[] = {16, 32};
+    for (int64_t total : totals) for (int64_t want : wants) for (int64_t unit : units) {
+        const auto c = coded::split_chunks(total, want, unit);
+        CHECK(c.per % unit == 0 && c.per >= 64 && c.count <= want, "split of %lld\n", static_cast<long long>(total));
+        int64_t at = 0;
+        for (int64_t i = 0; i < c.count; ++i) {
+            const uint32_t e0 = static_cast<uint32_t>(i) * static_cast<uint32_t>(c.per);
+            CHECK(e0 == at && at < total, "chunk %lld of %lld starts at %u\n", static_cast<long long>(i), static_cast<long long>(total), e0);
+            const uint32_t e1 = coded::chunk_end(e0, static_cast<uint32_t>(c.per), static_cast<uint32_t>(total));
+            CHECK(e1 > e0 && e1 <= total, "chunk %lld of %lld ends at %u\n", static_cast<long long>(i), static_cast<long long>(total), e1);
+            CHECK(static_cast<uint32_t>(e1 + 256 + 31) > e1, "tile steps past %u\n", e1);
+            at = e1;
+        }
+        CHECK(at == total, "%lld of %lld covered\n", static_cast<long long>(at), static_cast<long long>(total));
+    }
+}
+""")
