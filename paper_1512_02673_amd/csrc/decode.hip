@@ -26,7 +26,6 @@
 // otherwise, lanes on consecutive elements.
 #include "internal.h"
 #include "decode_common.h"
-#include "launch_rules.h"
 
 namespace coded {
 namespace {
@@ -815,7 +814,7 @@ hipError_t launch_fast(const DecodeArgs& a, const DecodeSet& single, hipStream_t
     const int64_t target = a.batch > 1 && std::min(a.k, a.n - a.k) > 4 ? 512 : 1024;
     const Chunks cut = split_chunks(total, ceil_div(target, a.batch), 16);
     const int64_t chunks = cut.count, blocks = chunks * a.batch;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     const int ksteps = (a.k + 3) / 4;
     const dim3 grid(static_cast<unsigned>(blocks));
     const int per32 = static_cast<int>(cut.per);
@@ -863,7 +862,7 @@ hipError_t launch_wide(const DecodeArgs& a, const DecodeSet& single, int mmax, h
     const int64_t total = a.qb * a.s;
     const Chunks cut = split_chunks(total, ceil_div(512, a.batch), 32);
     const int64_t blocks = cut.count * a.batch;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kWideThreads)) return hipErrorInvalidConfiguration;
     const int LD = std::max(mmax, 1) | 1;            // odd: columns start in different banks
     const size_t shmem = static_cast<size_t>(a.k + mmax) * LD * sizeof(double);
     const dim3 grid(static_cast<unsigned>(blocks));
@@ -886,13 +885,10 @@ size_t decode_lds_bytes(int k, int mmax) {
     return static_cast<size_t>(k * st + st * st + st) * sizeof(double);
 }
 
-hipError_t launch_decode(const DecodeArgs& a, const DecodeSet* single, int mmax, hipStream_t st) {
-    if (a.batch == 0) return hipSuccess;
-    if (a.qb * a.s > 0x7FFFFFFF) return hipErrorInvalidValue;
-    DecodeSet s{};
-    if (single) s = *single;
+// many: the sets are (part of) a batch of more than one.
+static hipError_t launch_sets(const DecodeArgs& a, bool many, const DecodeSet& s, int mmax, hipStream_t st) {
     const bool vec4 = a.s % 4 == 0 && a.ldo % 4 == 0 && aligned16(a.out) && aligned16(a.Y) &&
-                      (a.batch == 1 || a.out_stride % 4 == 0) && (a.c == nullptr || aligned16(a.c));
+                      (!many || a.out_stride % 4 == 0) && (a.c == nullptr || aligned16(a.c));
     // Outputs whose rows lie one after another are one column of q s elements,
     // taken four at a time at any alignment: 1000 (16,12) sets of 65536 x 1
     // 206 us one by one, 115 so; (32,24), 5000 x 5, 900 sets 85 and 48.  A single
@@ -901,7 +897,7 @@ hipError_t launch_decode(const DecodeArgs& a, const DecodeSet* single, int mmax,
     flat.qb = a.qb * a.s;
     flat.q = a.q * a.s;
     flat.s = flat.ldo = 1;
-    const bool dense = a.ldo == a.s && a.batch > 1 && flat.qb >= 4;
+    const bool dense = a.ldo == a.s && many && flat.qb >= 4;
     if (fast_path_ok(a)) {
         if (vec4) return launch_fast<4, false>(a, s, st);
         // read as a raw buffer: see ybuf in launch_fast
@@ -915,6 +911,22 @@ hipError_t launch_decode(const DecodeArgs& a, const DecodeSet* single, int mmax,
     if (mmax <= 16) return four ? launch_wide<1, 4>(w, s, mmax, st) : launch_wide<1, 1>(a, s, mmax, st);
     if (mmax <= 32) return four ? launch_wide<2, 4>(w, s, mmax, st) : launch_wide<2, 1>(a, s, mmax, st);
     return four ? launch_wide<4, 4>(w, s, mmax, st) : launch_wide<4, 1>(a, s, mmax, st);
+}
+
+hipError_t launch_decode(const DecodeArgs& a, const DecodeSet* single, int mmax, hipStream_t st) {
+    if (a.qb * a.s > 0x7FFFFFFF) return hipErrorInvalidValue;
+    DecodeSet s{};
+    if (single) s = *single;
+    for (int64_t b = 0; b < a.batch; b += kSetsPerLaunch) {
+        DecodeArgs part = a;
+        part.batch = static_cast<int32_t>(std::min(a.batch - b, kSetsPerLaunch));
+        part.info = a.info + b;
+        part.out = a.out + b * a.out_stride;
+        if (a.sets) part.sets = a.sets + b * a.k;
+        const hipError_t e = launch_sets(part, a.batch > 1, s, mmax, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace coded

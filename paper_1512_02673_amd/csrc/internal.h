@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/coded.h"
+#include "launch_rules.h"
 
 struct coded_code {
     int32_t n = 0, k = 0, planes = 2;

@@ -22,4 +22,12 @@ constexpr uint32_t chunk_end(uint32_t e0, uint32_t per, uint32_t total) {
     return e0 + (per < total - e0 ? per : total - e0);
 }
 
+// A launch counts the threads of each grid dimension modulo 2^32 and reports
+// nothing: one of 2^32 or more would leave work undone.
+constexpr bool grid_fits(int64_t blocks, int64_t threads) { return blocks <= ((int64_t(1) << 32) - 1) / threads; }
+
+// Survivor sets per launch.  The sets of a larger batch take one chunk each, so
+// a launch of 512-thread workgroups stays at half of what a grid takes.
+constexpr int64_t kSetsPerLaunch = int64_t(1) << 22;
+
 }  // namespace coded

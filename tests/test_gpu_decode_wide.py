@@ -106,6 +106,26 @@ def test_product_without_parity_workers(lib, torch, n, s):
     assert int(info) == 0 and torch.equal(out.view(q, s).double(), ref)
 
 
+@pytest.mark.parametrize("n,k,batch", [(34, 17, 2 ** 23 + 3), (16, 12, 2 ** 24 + 3)])
+def test_more_sets_than_one_grid_takes(lib, torch, n, k, batch):
+    """One set per workgroup of 512 threads (a wide code) or of 256: more than 2^32 threads."""
+    P = synth.integer_parity_matrix(n, k, 3)
+    B, Y = _results(P, k, k, 1, 5)
+    sets = torch.arange(k, dtype=torch.int32, device="cuda").repeat(batch, 1)
+    for b in (0, 2 ** 22 - 1, 2 ** 22, batch - 3, batch - 1):
+        sets[b, b % k] = k + int(np.flatnonzero(P[:, b % k])[0])
+    sets[batch - 2, 3] = n
+    out = torch.full((batch, k), -1.0, device="cuda")
+    info = torch.full((batch,), 9, dtype=torch.int32, device="cuda")
+    lib.coded_decode_batched(lib.Code.systematic(P, 2), sets, torch.from_numpy(Y).cuda(), k, out, info)
+    torch.cuda.synchronize()
+    assert int(info[batch - 2]) == -1 and torch.all(out[batch - 2] == -1.0)
+    info[batch - 2] = 0
+    out[batch - 2] = out[0]
+    assert torch.all(info == 0)
+    assert torch.equal(out, torch.from_numpy(B[:, 0].astype(np.float32)).cuda().expand(batch, k))
+
+
 # Blocks of 2^31 - 1 elements (the longest accepted): a copied block and a
 # recovered one, single elements and groups of four.
 @pytest.mark.parametrize("n,q,s", [(1, 2 ** 31 - 1, 1), (1, 2 ** 29 - 1, 4), (2, 2 ** 31 - 1, 1), (2, 2 ** 29 - 1, 4)])

@@ -11,7 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 def run_host(tmp_path, source):
     """Compile a host program against csrc/ and run it; a failed check or undefined behaviour ends it with an error."""
     src, exe = tmp_path / "check.cpp", tmp_path / "check"
-    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <cstdlib>\n"
+    src.write_text("#include <cstdint>\n#include <cstdio>\n#include <cstdlib>\n#include <initializer_list>\n"
                    "#define CHECK(c, ...) do { if (!(c)) { std::printf(__VA_ARGS__); std::exit(1); } } while (0)\n" + source)
     subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", f"-I{CSRC}",
                     str(src), "-o", str(exe)], check=True)
@@ -60,5 +60,24 @@ int main() {
         }
         CHECK(at == total, "%lld of %lld covered\n", static_cast<long long>(at), static_cast<long long>(total));
     }
+}
+""")
+
+
+def test_grids_stay_below_2_32_threads(tmp_path):
+    """Launches of the largest part of a batch, and the limit itself."""
+    run_host(tmp_path, r"""
+#include "launch_rules.h"
+int main() {
+    for (int threads : {64, 256, 512, 1024}) {
+        const int64_t most = ((1ll << 32) - 1) / threads;
+        CHECK(coded::grid_fits(most, threads) && most * threads < (1ll << 32), "%d threads\n", threads);
+        CHECK(!coded::grid_fits(most + 1, threads) && !coded::grid_fits(1ll << 62, threads), "%d threads\n", threads);
+    }
+    for (int64_t batch : {coded::kSetsPerLaunch, coded::kSetsPerLaunch - 1, int64_t(1000), int64_t(1)})
+        for (int64_t total : {int64_t(1), int64_t(1000), (int64_t(1) << 31) - 1}) {
+            const auto c = coded::split_chunks(total, (1024 + batch - 1) / batch, 16);
+            CHECK(coded::grid_fits(c.count * batch, 512), "%lld sets of %lld\n", static_cast<long long>(batch), static_cast<long long>(total));
+        }
 }
 """)
