@@ -276,7 +276,7 @@ hipError_t launch_encode_f32(const EncodeArgs& a, hipStream_t st) {
     const int width = row_threads(a.r, V);
     const int64_t rows = ceil_div(a.qb, kThreads / width);
     const int64_t blocks = groups > 1 ? ceil_div(rows, 8) * 8 * groups : rows;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(chunks));
     if (vec)
         hipLaunchKernelGGL(encode_f32_kernel<4>, grid, dim3(kThreads), 0, st, a, groups, width);
@@ -296,7 +296,7 @@ hipError_t launch_encode_bf16(const EncodeArgs& a, hipStream_t st) {
     const int width = row_threads(a.r, V);
     const int64_t rows = ceil_div(a.qb, kThreads / width);
     const int64_t blocks = groups > 1 ? ceil_div(rows, 8) * 8 * groups : rows;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     dim3 grid(static_cast<unsigned>(blocks), static_cast<unsigned>(chunks));
     if (vec)
         hipLaunchKernelGGL(encode_bf16_kernel<8>, grid, dim3(kThreads), 0, st, a, groups, width);

@@ -446,7 +446,7 @@ hipError_t launch_single_pass(FusedArgs a, bool products, int compute_units, hip
     // tiles whose 16 rows lie inside every block (no clamped or zeroed row)
     const int64_t lim = std::min(a.qb, a.q - static_cast<int64_t>(a.k - 1) * a.qb);
     a.clean_tiles = lim > 0 ? lim / 16 : 0;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kWaves * 64)) return hipErrorInvalidConfiguration;
     if (products)
         hipLaunchKernelGGL((fused_bf16_kernel<kWaves, 24, 8, true>), dim3(static_cast<unsigned>(blocks)),
                            dim3(kWaves * 64), 0, st, a);
@@ -468,8 +468,9 @@ hipError_t launch_fused_bf16(FusedArgs a, bool products, int compute_units, hipS
     if (a.qb == 0 || a.r == 0) return hipSuccess;
     if (products) {
         const int64_t ny = static_cast<int64_t>(a.n) * a.qb * 64;
-        hipLaunchKernelGGL(zero_f32_kernel, dim3(static_cast<unsigned>(ceil_div(ny, 4 * 256))), dim3(256), 0, st, a.Y,
-                           ny);
+        const int64_t zblocks = ceil_div(ny, 4 * 256);
+        if (!grid_fits(zblocks, 256)) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL(zero_f32_kernel, dim3(static_cast<unsigned>(zblocks)), dim3(256), 0, st, a.Y, ny);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -482,7 +483,7 @@ hipError_t launch_fused_bf16_from_x(FusedArgs a, const uint16_t* X, int64_t s, i
     const int64_t tiles_s = ceil_div(s, 64), ttiles = ceil_div(a.r, 64) * tiles_s;
     const int64_t ny = static_cast<int64_t>(a.n) * a.qb * 64;
     const int64_t blocks = ttiles + ceil_div(ny, 16384);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, 256)) return hipErrorInvalidConfiguration;
     const int vec = s == 64 && a.r % 64 == 0 && ldx % 8 == 0 && (reinterpret_cast<uintptr_t>(X) & 15u) == 0 &&
                     (reinterpret_cast<uintptr_t>(a.xt) & 15u) == 0;
     hipLaunchKernelGGL(fused_prep_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, X, a.r, s, ldx,

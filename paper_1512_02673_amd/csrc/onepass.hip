@@ -333,7 +333,7 @@ bool onepass_supported(int n, int k, int64_t q, int64_t r, int64_t lda, const vo
 
 hipError_t launch_onepass_f32(const OnePassArgs& a, hipStream_t st) {
     if (a.qb == 0) return hipSuccess;
-    if (a.qb > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(a.qb, 256)) return hipErrorInvalidConfiguration;
     // Wave 0 forms D while the others stream: one streaming wave per 256
     // columns up to two, then three.
     const dim3 grid(static_cast<unsigned>(a.qb));

@@ -277,11 +277,18 @@ __global__ __launch_bounds__(256) void runtime_sim_kernel(int n, int k, uint64_t
 template <int N, int LOW>
 hipError_t launch_sim(int n, int k, uint64_t seed, uint64_t first, int64_t count, const SimConst& c, double* tu,
                       double* tr, double* tm, hipStream_t st) {
-    const int64_t blocks = ceil_div(count, 256);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((runtime_sim_kernel<N, LOW>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, n, k, seed,
-                       first, count, c, tu, tr, tm);
-    return hipGetLastError();
+    // a grid takes fewer than 2^32 draws
+    constexpr int64_t kMost = int64_t(1) << 31;
+    for (int64_t d = 0; d < count; d += kMost) {
+        const int64_t part = count - d < kMost ? count - d : kMost, blocks = ceil_div(part, 256);
+        if (!grid_fits(blocks, 256)) return hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((runtime_sim_kernel<N, LOW>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, n, k, seed,
+                           first + static_cast<uint64_t>(d), part, c, tu ? tu + d : nullptr, tr ? tr + d : nullptr,
+                           tm ? tm + d : nullptr);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // The smallest instance of N, ... that holds n.

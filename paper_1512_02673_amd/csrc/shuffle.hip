@@ -230,7 +230,7 @@ hipError_t launch_shuffle_encode(const float* A, int64_t q, int64_t r, int64_t l
                                  hipStream_t st) {
     if (msgs == 0 || r == 0) return hipSuccess;
     const int64_t blocks = ceil_div(msgs, kWaves);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     if (by_vectors(r, lda, ldm, 0, A, M, nullptr))
         hipLaunchKernelGGL(shuffle_encode_kernel<4>, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, A, q,
                            r, lda, off, rows, msgs, terms, M, ldm);
@@ -245,7 +245,7 @@ hipError_t launch_shuffle_decode(const float* A, int64_t q, int64_t r, int64_t l
                                  int64_t terms, float* out, int64_t ldo, hipStream_t st) {
     if (terms == 0 || msgs == 0 || r == 0) return hipSuccess;
     const int64_t blocks = ceil_div(msgs, kWaves);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     if (by_vectors(r, lda, ldm, ldo, A, M, out))
         hipLaunchKernelGGL(shuffle_decode_kernel<4>, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, A, q,
                            r, lda, M, ldm, off, rows, msg, msgs, terms, out, ldo);

@@ -34,7 +34,7 @@ hipError_t launch_transpose_f32(const float* A, int64_t q, int64_t r, int64_t ld
                                 hipStream_t st) {
     if (q == 0 || r == 0) return hipSuccess;
     const int64_t tq = ceil_div(q, kTile), tr = ceil_div(r, kTile);
-    if (tq * tr > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(tq * tr, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(transpose_f32_kernel, dim3(static_cast<unsigned>(tq * tr)), dim3(256), 0, st, A, q, r, lda, AT,
                        ldat, tr);
     return hipGetLastError();

@@ -418,7 +418,7 @@ hipError_t launch_waves(K kernel, const WorkerArgs& a, int64_t wsys, int64_t wpa
     const int64_t waves = wsys * a.n_sys + wpar * a.n_par;
     if (waves == 0) return hipSuccess;
     const int64_t blocks = ceil_div(waves, kWaves);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
@@ -436,7 +436,7 @@ template <int T, int XR, bool LO16, bool NTL, bool TAIL>
 static hipError_t launch_gemv_v(const WorkerArgs& a, hipStream_t st) {
     const int64_t blocks = ceil_div(a.qb, T) * (a.n_sys + a.n_par);
     if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, 256)) return hipErrorInvalidConfiguration;
     // Rows of 8 column slots per thread that stream from HBM: at most three
     // workgroups per compute unit (each requests 40 KB of the 160 KB of LDS,
     // which it does not use), which streams these long rows best (measured:
@@ -453,7 +453,7 @@ template <int T, int XR, int LPR, bool LO16, bool NTL, bool TAIL>
 static hipError_t launch_short_v(const WorkerArgs& a, hipStream_t st) {
     const int64_t blocks = ceil_div(a.qb, 256 / LPR * T) * (a.n_sys + a.n_par);
     if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((gemv_short_kernel<T, XR, LPR, LO16, NTL, TAIL>), dim3(static_cast<unsigned>(blocks)), dim3(256),
                        0, st, a);
     return hipGetLastError();

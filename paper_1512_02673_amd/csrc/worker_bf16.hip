@@ -389,7 +389,7 @@ hipError_t launch_waves(K kernel, const WorkerArgs& a, int64_t wsys, int64_t wpa
     const int64_t waves = wsys * a.n_sys + wpar * a.n_par;
     if (waves == 0) return hipSuccess;
     const int64_t blocks = ceil_div(waves, kWaves);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
@@ -411,7 +411,7 @@ static hipError_t launch_bf16_mm(const WorkerArgs& a, int64_t c0, hipStream_t st
     const int64_t ptiles = ceil_div(a.qb, a.planes == 2 ? 8 * RT : 16 * RT);
     const int64_t blocks = stiles * a.n_sys + ptiles * a.n_par;
     if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((gemm_bf16_mfma_kernel<RT, NT, KC, PF, WK, NTL>), dim3(static_cast<unsigned>(blocks)),
                        dim3(kThreads), 0, st, a, stiles, ptiles, c0);
     return hipGetLastError();

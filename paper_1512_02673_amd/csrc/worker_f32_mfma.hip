@@ -419,7 +419,7 @@ hipError_t launch_mm(const WorkerArgs& a, int64_t c0, hipStream_t st, int64_t co
     const int64_t ptiles = a.planes == 2 ? ceil_div(a.qb, C::kRows / 2) : stiles;
     const int64_t blocks = stiles * a.n_sys + ptiles * a.n_par;
     if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kMmThreads)) return hipErrorInvalidConfiguration;
     auto go = [&](auto buf, auto tail) {
         hipLaunchKernelGGL((gemm_f32_mfma_kernel<RT, NCT, NARROW, KC, PF, decltype(buf)::value, decltype(tail)::value>),
                            dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(col_tiles)), dim3(kMmThreads), 0,

@@ -76,3 +76,15 @@ def test_single_outputs(lib, torch):
         lib.coded_simulate_runtimes(n, k, 5, 0, *one)
         torch.cuda.synchronize()
         assert torch.equal(one[i], both[i])
+
+
+def test_more_draws_than_one_grid_takes(lib, torch):
+    """2^32 + 5 draws: windows around the ends of the launches, and no draw left out."""
+    n, k, count = 2, 1, 2 ** 32 + 5
+    tm = torch.full((count,), -1.0, dtype=torch.float64, device="cuda")
+    lib.coded_simulate_runtimes(n, k, 3, 0, None, None, tm)
+    assert float(tm.min()) >= 1.0
+    for first, size in ((0, 1000), (2 ** 31 - 300, 600), (2 ** 32 - 300, 305)):
+        part = torch.empty(size, dtype=torch.float64, device="cuda")
+        lib.coded_simulate_runtimes(n, k, 3, first, None, None, part)
+        assert torch.equal(part, tm[first:first + size])
