@@ -441,20 +441,23 @@ bool gemm_f32_mfma_supported(const WorkerArgs& a) {
     return a.s > 1 && !a.lo_bf16 && a.r >= 4 && a.r <= (1ll << 30);
 }
 
-// Up to 8 columns: 4-column tiles, one launch.  More: 16-column tiles in
-// launches of at most 32 columns (two 32-column launches measured faster
-// than one 64-column launch at s = 64: the wider tile halves occupancy).
-// Few rows (fewer than 256 workgroups of 32 rows): the K loop of one workgroup
-// bounds the call, so tiles of 16 rows x 16 columns (or x 4, 256 k per chunk),
-// all columns in one launch, and four chunks in flight.  A (3,2) code on 777 x
-// 16000, 33 columns: 134 us against 372; (32,24), 100 x 8000, 40 columns: 44
-// against 175; (4,2), 64 x 16000, 8 columns: 44 against 70; at 768 workgroups
-// ((20,16), 16384 x 4096, 64 columns) 376 against 237.
+// Streamed launches: up to 8 columns in 4-column tiles; more in 16-column tiles
+// of launches of at most 32 columns (two 32-column launches measured faster than
+// one 64-column launch at s = 64: the wider tile halves occupancy).  The other
+// tiles, for launches that would leave the chip idle: see column_tiles.  A
+// (3,2) code on 777 x 16000, 33 columns: 134 us against 372 streamed; (32,24),
+// 100 x 8000, 40 columns: 44 against 175; (4,2), 64 x 16000, 8 columns: 44
+// against 70.
 hipError_t launch_gemm_f32_mfma(const WorkerArgs& a, hipStream_t st) {
-    const int64_t rows = a.qb * (a.n_sys + (a.planes == 2 ? 2 : 1) * a.n_par);
-    if (rows < 256 * 32 && ceil_div(a.s, 4) <= 65535)
-        return a.s <= 8 ? launch_mm<1, 1, true, 256, 4>(a, 0, st, ceil_div(a.s, 4))
-                        : launch_mm<1, 1, false, 128, 4>(a, 0, st, ceil_div(a.s, 16));
+    const int64_t slots = a.planes == 2 ? 2 : 1;           // row slots of a parity worker's block row
+    auto blocks = [&](int64_t rows) { return ceil_div(a.qb, rows) * a.n_sys + ceil_div(a.qb, rows / slots) * a.n_par; };
+    switch (column_tiles(blocks(16), blocks(32), a.s)) {
+        case ColumnTiles::kLongK4: return launch_mm<1, 1, true, 256, 4>(a, 0, st, ceil_div(a.s, 4));
+        case ColumnTiles::kShort4: return launch_mm<1, 1, true, 128, 4>(a, 0, st, ceil_div(a.s, 4));
+        case ColumnTiles::kShort16: return launch_mm<1, 1, false, 128, 4>(a, 0, st, ceil_div(a.s, 16));
+        case ColumnTiles::kWide32: return launch_mm<2, 2, false, 64, 2>(a, 0, st, ceil_div(a.s, 32));
+        case ColumnTiles::kStream: break;
+    }
     if (a.s <= 4) return launch_mm<1, 1, true, 128, 4>(a, 0, st);
     if (a.s <= 8) return launch_mm<1, 2, true, 128, 2>(a, 0, st);
     for (int64_t c0 = 0; c0 < a.s; c0 += 32) {

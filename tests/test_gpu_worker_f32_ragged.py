@@ -62,7 +62,13 @@ def test_strides_and_alignment(lib, torch, apad, xpad, lead, r, s):
 
 # several tiles with a ragged last one; blocks of padding only; no parity; one row per block
 @pytest.mark.parametrize("n,k,q,r,s", [(20, 16, 1999, 131, 20), (64, 48, 49, 70, 9), (4, 4, 33, 131, 7), (5, 3, 1, 90, 3),
-                                       (64, 48, 700, 257, 32)])
+                                       (64, 48, 700, 257, 32),
+                                       # both sides of the tile rules: 16 x 4 tiles up to 256 workgroups (4 columns)
+                                       # and up to 192 and 384 (8), 16 x 16 tiles, 32 x 32 in one launch with a last
+                                       # tile of 1 and of 17 columns, and launches of 32 columns
+                                       (20, 16, 2300, 70, 4), (20, 16, 2800, 70, 4), (20, 16, 1000, 70, 8), (20, 16, 1500, 70, 8),
+                                       (20, 16, 2900, 70, 8), (20, 16, 2000, 66, 96), (20, 16, 3000, 66, 65),
+                                       (20, 16, 3000, 66, 49), (20, 16, 9000, 65, 49), (4, 2, 2666, 65, 20)])
 def test_tiles(lib, torch, n, k, q, r, s):
     got, ref = _run(lib, torch, n, k, q, r, s, 2)
     assert np.array_equal(got, ref)

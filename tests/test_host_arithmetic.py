@@ -81,3 +81,29 @@ int main() {
         }
 }
 """)
+
+
+def test_column_tiles_count_the_columns(tmp_path):
+    """The small tiles of the fp32 products re-read A once per column tile: they are for launches
+    whose workgroups, column tiles counted, leave compute units idle."""
+    run_host(tmp_path, r"""
+#include "launch_rules.h"
+using namespace coded;
+int main() {
+    const int codes[][2] = {{20, 16}, {4, 2}, {3, 2}, {64, 48}, {128, 96}, {10, 10}};
+    for (const auto& c : codes) for (int64_t qb : {1, 8, 16, 17, 40, 80, 83, 125, 200, 250, 300, 333, 600, 1333, 1400, 5000, 100000})
+        for (int64_t s : {2, 4, 5, 8, 9, 16, 17, 32, 33, 64, 96, 200, 1000, 300000}) {
+            const int64_t k = c[1], p = c[0] - c[1];
+            const int64_t rows = k * ((qb + 15) / 16) + p * ((qb + 7) / 8), rows32 = k * ((qb + 31) / 32) + p * ((qb + 15) / 16);
+            const auto t = column_tiles(rows, rows32, s);
+            const int64_t n4 = rows * ((s + 3) / 4), n16 = rows * ((s + 15) / 16);
+            auto check = [&](bool ok) { CHECK(ok, "(%d,%d) qb %ld s %ld\n", c[0], c[1], (long)qb, (long)s); };
+            if (t == ColumnTiles::kLongK4) check(s <= 8 && n4 <= 256);
+            if (t == ColumnTiles::kShort4) check(s > 4 && s <= 8 && n4 <= 384);
+            if (t == ColumnTiles::kShort16) check(s > 8 && (n16 <= 768 || (s > 16 && 35 * n16 <= 64 * (350 + rows32 * ((s + 31) / 32)))));
+            if (t == ColumnTiles::kWide32) check(s > 16 && (s + 31) / 32 <= 65535);
+            if (rows > 768) check(t == ColumnTiles::kStream);
+            if (s > 8 && s <= 300 && n16 <= 768) check(t == ColumnTiles::kShort16);
+        }
+}
+""")
