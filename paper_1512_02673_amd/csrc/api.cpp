@@ -149,9 +149,16 @@ coded_status do_encode(const coded_code* c, coded_dtype dt, const void* A, int64
     return CODED_OK;
 }
 
+int64_t operand_bytes_of(const coded_code* c, coded_dtype dt, int64_t q, int64_t r) {
+    const int64_t size = static_cast<int64_t>(dtype_size(dt));
+    const int64_t parity = c->lo_bf16 && dt == CODED_F32 ? 6 : c->planes * size;
+    return operand_bytes(q, r, block_rows(q, c->k), c->n - c->k, size, parity);
+}
+
+// beside: bytes of the other operands the caller goes through between two of these products.
 coded_status do_workers(const coded_code* c, coded_dtype dt, const void* A, int64_t q, int64_t r, int64_t lda,
                         const void* parity, const void* X, int64_t s, int64_t ldx, const uint8_t* mask, void* Y,
-                        coded_dtype y_dt, hipStream_t st) {
+                        coded_dtype y_dt, hipStream_t st, int64_t beside = 0) {
     if (s < 0) return fail(CODED_ERR_SHAPE, "s must be >= 0");
     if (ldx < std::max<int64_t>(s, 1)) return fail(CODED_ERR_SHAPE, "ldx must be >= max(s, 1)");
     if (s == 1 && ldx != 1 && dt == CODED_F32) {
@@ -182,6 +189,7 @@ coded_status do_workers(const coded_code* c, coded_dtype dt, const void* A, int6
     a.planes = c->planes;
     a.lo_bf16 = c->lo_bf16 && dt == CODED_F32;
     a.y_f64 = y_dt == CODED_F64;
+    a.stream = streams(operand_bytes_of(c, dt, q, r) + beside);
     for (int i = 0; i < c->n; ++i) {
         if (mask && !mask[i]) continue;
         if (i < c->k)
@@ -820,10 +828,14 @@ coded_status coded_gd_step(const coded_code* cA, const coded_code* cT, const flo
     float* z = reinterpret_cast<float*>(reinterpret_cast<char*>(Y2) +
                                         align256(static_cast<int64_t>(cT->n) * block_rows(r, cT->k) * 8));
     // z = A x - y  (coded product with code A, residual fused into the decode)
-    if (coded_status e = do_workers(cA, CODED_F32, A, q, r, lda, parityA, x, 1, 1, nullptr, Y1, CODED_F64, st)) return e;
+    if (coded_status e = do_workers(cA, CODED_F32, A, q, r, lda, parityA, x, 1, 1, nullptr, Y1, CODED_F64, st,
+                                    operand_bytes_of(cT, CODED_F32, r, q)))
+        return e;
     if (coded_status e = do_decode_single(cA, set1, m1, Y1, CODED_F64, q, 1, z, 1, info, st, y, 1.0, -1.0)) return e;
     // x = x - eta A^T z  (coded product with the code of A^T, update fused into the decode)
-    if (coded_status e = do_workers(cT, CODED_F32, AT, r, q, ldat, parityAT, z, 1, 1, nullptr, Y2, CODED_F64, st)) return e;
+    if (coded_status e = do_workers(cT, CODED_F32, AT, r, q, ldat, parityAT, z, 1, 1, nullptr, Y2, CODED_F64, st,
+                                    operand_bytes_of(cA, CODED_F32, q, r)))
+        return e;
     if (coded_status e = do_decode_single(cT, set2, m2, Y2, CODED_F64, r, 1, x, 1, info + 1, st, x, -eta, 1.0)) return e;
     if (survivors_out) {
         std::copy(s1, s1 + cA->k, survivors_out);

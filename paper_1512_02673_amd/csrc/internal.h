@@ -59,6 +59,7 @@ struct WorkerArgs {
     int32_t y_f64;        // 1: Y is fp64, 0: Y is fp32
     int32_t n_sys, n_par; // active systematic / parity workers
     int32_t lo_bf16;      // fp32 with planes == 2: the lo plane is bfloat16 (after the fp32 hi plane)
+    int32_t stream;       // 1: A and the planes do not stay in the memory-side cache between calls (non-temporal loads)
     uint8_t sys_ids[kMaxN];
     uint8_t par_ids[kMaxN];
 };

@@ -65,6 +65,18 @@ constexpr ColumnTiles column_tiles(int64_t blocks16, int64_t blocks32, int64_t s
     return quicker ? ColumnTiles::kShort16 : ColumnTiles::kWide32;
 }
 
+// Bytes of A and of the parity planes a code holds for it: `size` bytes an
+// element, `parity_size` for a parity element of every plane.
+constexpr int64_t operand_bytes(int64_t q, int64_t r, int64_t qb, int64_t parity_workers, int64_t size, int64_t parity_size) {
+    return (q * size + parity_workers * qb * parity_size) * r;
+}
+
+// Loads of A and the planes: non-temporal when what a caller goes through before
+// it returns to the same bytes (every worker's block, and every matrix of an
+// iteration) does not fit the 256 MB memory-side cache, whatever part of it one
+// launch reads; plain loads while it fits, where the next call finds it.
+constexpr bool streams(int64_t bytes) { return bytes > (int64_t(256) << 20); }
+
 // Survivor sets per launch.  The sets of a larger batch take one chunk each, so
 // a launch of 512-thread workgroups stays at half of what a grid takes.
 constexpr int64_t kSetsPerLaunch = int64_t(1) << 22;

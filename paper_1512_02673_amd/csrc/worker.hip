@@ -15,7 +15,6 @@
 // 154).  Products of two fp32 values are exact in fp64 and are summed in fp64.
 // s > 1 runs on the fp64 matrix cores (worker_f32_mfma.hip); what that cannot
 // take runs a general vector kernel.
-#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -425,13 +424,6 @@ hipError_t launch_waves(K kernel, const WorkerArgs& a, int64_t wsys, int64_t wpa
 
 }  // namespace
 
-// What a launch of products reads from A and the parity planes.
-static int64_t read_bytes(const WorkerArgs& a) {
-    const int64_t par = static_cast<int64_t>(a.n_par) * a.qb * a.r;
-    const int64_t planes = a.planes == 1 ? 4 : (a.lo_bf16 ? 6 : 8);
-    return 4 * a.r * std::min(a.q, a.n_sys * a.qb) + planes * par;
-}
-
 template <int T, int XR, bool LO16, bool NTL, bool TAIL>
 static hipError_t launch_gemv_v(const WorkerArgs& a, hipStream_t st) {
     const int64_t blocks = ceil_div(a.qb, T) * (a.n_sys + a.n_par);
@@ -460,13 +452,12 @@ static hipError_t launch_short_v(const WorkerArgs& a, hipStream_t st) {
 }
 
 // The plane format, the tail and the cache policy as template arguments.
-// Plain loads while everything read fits the 256 MB memory-side cache, where
-// the next call finds it; non-temporal loads above (65536 x 8192: 522 us
+// Non-temporal loads where the operands are streamed (65536 x 8192: 522 us
 // against 587 with plain loads).
 template <int T, int XR, int LPR>
 static hipError_t launch_gemv_any(const WorkerArgs& a, hipStream_t st) {
     const bool lo16 = a.lo_bf16 && a.planes == 2, tail = a.r % 4 != 0;
-    const bool ntl = read_bytes(a) > (256ll << 20);
+    const bool ntl = a.stream;
     auto go = [&](auto lo, auto nt, auto tl) {
         constexpr bool L = decltype(lo)::value, N = decltype(nt)::value, TL = decltype(tl)::value;
         if constexpr (LPR == 256)

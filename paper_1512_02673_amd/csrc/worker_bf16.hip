@@ -421,11 +421,10 @@ hipError_t launch_worker_bf16(const WorkerArgs& a, hipStream_t st) {
     if (a.qb == 0 || a.s == 0) return hipSuccess;
     // rows shorter than one 16-byte piece (and empty A, or K past 32 bits)
     if (a.r < 8 || a.r > (1ll << 30) || a.q == 0) return launch_waves(gemm_small_bf16_kernel<4>, a, a.qb, a.qb, st);
-    // What a launch reads.  Past the 256 MB memory-side cache nothing of it is
-    // left for the next call, and non-temporal loads stream it faster (1.2 GB
-    // with 4 columns: 182 us against 200); below, plain loads find it there
-    // (155 MB with 16 columns: 28 us against 35).
-    const bool stream = 2 * a.r * (a.q + static_cast<int64_t>(a.planes) * a.n_par * a.qb) > (256ll << 20);
+    // Operands past the memory-side cache stream faster with non-temporal loads
+    // (1.2 GB with 4 columns: 182 us against 200); below, plain loads find them
+    // there (155 MB with 16 columns: 28 us against 35).
+    const bool stream = a.stream;
     for (int64_t c0 = 0; c0 < a.s; c0 += 64) {
         const int64_t cols = std::min<int64_t>(64, a.s - c0);
         hipError_t e;

@@ -107,3 +107,21 @@ int main() {
         }
 }
 """)
+
+
+def test_cache_policy_takes_the_whole_operands(tmp_path):
+    """Every worker's block and plane counts, whichever of them a launch reads: one worker of
+    65536 x 8192 reads 179 MB, the 16 of them 3.6 GB."""
+    run_host(tmp_path, r"""
+#include "launch_rules.h"
+using namespace coded;
+int main() {
+    const int64_t qb = (65536 + 11) / 12;
+    const int64_t all = operand_bytes(65536, 8192, qb, 4, 4, 8);
+    CHECK(all == 65536ll * 8192 * 4 + 4 * qb * 8192 * 8 && streams(all), "%ld\n", (long)all);
+    CHECK(qb * 8192 * 4 < (256ll << 20), "one worker alone would not stream\n");
+    CHECK(operand_bytes(10, 7, 5, 2, 4, 6) == 10 * 7 * 4 + 2 * 5 * 7 * 6, "a bfloat16 lo plane\n");
+    CHECK(operand_bytes(10, 7, 5, 0, 2, 4) == 10 * 7 * 2, "no parity workers\n");
+    CHECK(!streams(256ll << 20) && streams((256ll << 20) + 1), "the cache's size\n");
+}
+""")
