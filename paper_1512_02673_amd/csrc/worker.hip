@@ -434,8 +434,12 @@ static hipError_t launch_gemv_v(const WorkerArgs& a, hipStream_t st) {
     // which it does not use), which streams these long rows best (measured:
     // two, three and four; 65536 x 8192: 521.8 us against 524.1 without).
     // From the memory-side cache the limit costs (1472 x 7307: 12.5 us
-    // against 10.7).
-    const size_t cap = XR >= 8 && NTL ? 40 * 1024 : 0;
+    // against 10.7).  Rows of 6 slots want it when whole and well filled
+    // ((4,2), 420 and 840 MB of A: r = 5752 452 and 909 us against 472 and 950,
+    // r = 5000 449 against 467), not with a remainder (r = 5750: 519 against
+    // 467) nor near 4 slots ((16,12), r = 4352: 252 against 247).
+    const bool whole6 = XR == 6 && !TAIL && a.r > 4608;
+    const size_t cap = NTL && (XR >= 8 || whole6) ? 40 * 1024 : 0;
     hipLaunchKernelGGL((gemv_wg_kernel<T, XR, 256, LO16, NTL, TAIL>), dim3(static_cast<unsigned>(blocks)), dim3(256),
                        cap, st, a);
     return hipGetLastError();
