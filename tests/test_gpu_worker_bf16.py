@@ -81,6 +81,57 @@ def test_strides_and_alignment(lib, torch, apad, xpad, lead, r, s):
     _check(lib, torch, 5, 3, 70, r, s, 2, apad, xpad, lead)
 
 
+# Rows of whole 16-byte pieces that take one step of K (up to 224 elements; 256
+# with up to 32 columns, 384 with up to 16), either side of the steps of 64, one
+# and two column tiles traded between rows, column remainders of 1 to 3, blocks
+# of less than a 16-row tile and of more than a workgroup's 256 slots, padding
+# rows, odd strides of X.
+@pytest.mark.parametrize("r", [8, 56, 64, 72, 128, 136, 192, 200, 224, 232, 256, 264, 320, 328, 384, 392])
+@pytest.mark.parametrize("s", [1, 2, 15, 17, 31, 33, 47, 48, 62, 64, 67])
+def test_short_rows(lib, torch, r, s):
+    _check(lib, torch, 6, 4, 1131, r, s, 2, xpad=s % 3)
+
+
+@pytest.mark.parametrize("n,k,q,planes", [(5, 3, 2, 2), (4, 4, 45, 2), (64, 48, 47, 2), (6, 4, 2049, 1), (3, 1, 300, 2)])
+@pytest.mark.parametrize("r,s", [(64, 5), (160, 64), (256, 20), (384, 16)])
+def test_short_row_blocks(lib, torch, n, k, q, planes, r, s):
+    _check(lib, torch, n, k, q, r, s, planes, apad=8)
+
+
+def test_short_row_mask(lib, torch):
+    mask = np.zeros(16, dtype=np.uint8)
+    mask[[1, 11, 13, 15]] = 1
+    for r, s in ((72, 40), (264, 3)):
+        _check(lib, torch, 16, 12, 700, r, s, 2, mask=mask)
+
+
+# Enough rows for the tiles of 64 and 128 rows (512 and 1024 workgroups of 128),
+# rows past the short ones and, from 256 MB on, streamed ones.  Checked on the
+# GPU in fp64, exact for the integers.
+@pytest.mark.parametrize("q,r,s", [(50000, 270, 33), (50000, 264, 20), (110000, 330, 64), (110000, 264, 20), (110000, 400, 130),
+                                   (230000, 400, 1), (230000, 648, 3), (190000, 776, 17), (120000, 1100, 33),
+                                   (70000, 2048, 48), (45000, 2056, 48)])
+def test_many_rows(lib, torch, q, r, s):
+    n, k = 20, 16
+    gen = torch.Generator(device="cuda").manual_seed(q + r + s)
+    A = torch.randint(-3, 4, (q, r), device="cuda", generator=gen).bfloat16()
+    X = torch.randint(-3, 4, (r, s), device="cuda", generator=gen).bfloat16()
+    P = torch.randint(-2, 3, (n - k, k), device="cuda", generator=gen).double()
+    code = lib.Code.systematic(P.cpu().numpy(), 2)
+    par = lib.alloc_parity(code, q, r, torch.bfloat16)
+    lib.coded_encode(code, A, par)
+    qb = code.qb(q)
+    B = torch.zeros((k * qb, s), dtype=torch.float64, device="cuda")
+    for i in range(0, q, 20000):
+        B[i:min(q, i + 20000)] = A[i:i + 20000].double() @ X.double()
+    B = B.view(k, qb * s)
+    ref = torch.cat([B, P @ B]).view(n, qb, s)
+    Y = lib.alloc_y(code, q, s, torch.float32)
+    Y.fill_(float("nan"))
+    lib.coded_worker_mm(code, A, par, X if s > 1 else X.view(-1), Y)
+    assert torch.equal(Y.view(n, qb, s).double(), ref)
+
+
 def test_mask(lib, torch):
     mask = np.zeros(16, dtype=np.uint8)
     mask[[0, 11, 12, 15]] = 1
