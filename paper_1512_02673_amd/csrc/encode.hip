@@ -40,11 +40,20 @@ typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned int u32x4e __attribute__((ext_vector_type(4), aligned(2)));
 typedef unsigned int u32x2e __attribute__((ext_vector_type(2), aligned(2)));
 
-// Threads per block row (a workgroup takes kThreads / that many rows).
+// Threads per block row (a workgroup takes kThreads / that many rows; one row
+// without the division that tells several apart).
 int row_threads(int64_t r, int vec) {
     const int64_t v = ceil_div(r, vec);
-    return v < kThreads ? static_cast<int>(v) : kThreads;
+    return 2 * v <= kThreads ? static_cast<int>(v) : kThreads;
 }
+
+// Small planes take one column a thread: with few threads the call lasts as long
+// as one of them walks its k blocks, eight parity sums for every column it owns
+// (elements of a plane times groups; (32,24) on 2000 x 257 bf16 17.0 us with eight
+// columns a thread, 11.5 with one; (128,96) on 8000 x 400, 134400, 56.8 and 41.7;
+// (16,12) on 8000 x 400, 266800, 7.9 and 8.1; fp32 (128,96) on 8000 x 200, 67200,
+// 44.9 and 43.0).
+constexpr int64_t kSingleF32 = 96 << 10, kSingleBf16 = 256 << 10;
 
 // The workgroup's row index (in units of the rows it takes) and first parity
 // row.  Workgroups go to the 8 XCDs in turn, so the groups of parity rows that
@@ -269,7 +278,7 @@ hipError_t launch_encode_f32(const EncodeArgs& a, hipStream_t st) {
     const int npar = a.n - a.k;
     if (npar == 0 || a.qb == 0 || a.r == 0) return hipSuccess;
     const int groups = static_cast<int>(ceil_div(npar, kGroup));
-    const bool vec = a.r >= 4;
+    const bool vec = a.r >= 4 && a.qb * a.r * groups > kSingleF32;
     const int V = vec ? 4 : 1;
     const int64_t chunks = ceil_div(a.r, static_cast<int64_t>(kThreads) * V);
     if (chunks * groups > 65535) return hipErrorInvalidConfiguration;
@@ -289,7 +298,7 @@ hipError_t launch_encode_bf16(const EncodeArgs& a, hipStream_t st) {
     const int npar = a.n - a.k;
     if (npar == 0 || a.qb == 0 || a.r == 0) return hipSuccess;
     const int groups = static_cast<int>(ceil_div(npar, kGroup));
-    const bool vec = a.r >= 8;
+    const bool vec = a.r >= 8 && a.qb * a.r * groups > kSingleBf16;
     const int V = vec ? 8 : 1;
     const int64_t chunks = ceil_div(a.r, static_cast<int64_t>(kThreads) * V);
     if (chunks * groups > 65535) return hipErrorInvalidConfiguration;

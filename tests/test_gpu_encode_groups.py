@@ -24,7 +24,13 @@ def torch():
 # two groups (one partial) and more; one, seven, eight, nine and seventeen block rows; several rows per
 # workgroup, one, and several column chunks
 @pytest.mark.parametrize("n,k,q,r", [(12, 3, 3, 40), (19, 10, 70, 1024), (64, 48, 48 * 8, 2050), (30, 7, 7 * 9 - 2, 3000),
-                                     (128, 64, 64 * 17 - 5, 33), (40, 4, 4 * 131, 9), (20, 2, 34, 3)])
+                                     (128, 64, 64 * 17 - 5, 33), (40, 4, 4 * 131, 9), (20, 2, 34, 3),
+                                     # planes past the sizes that take one column a thread (96 Ki elements times
+                                     # groups in fp32, 256 Ki in bf16), and either side of them
+                                     (12, 3, 3 * 4000, 40), (64, 48, 48 * 70, 2050), (30, 7, 7 * 40 - 3, 3000),
+                                     (128, 64, 64 * 1100 - 5, 33), (40, 4, 4 * 6100, 9), (4, 3, 3 * 1024, 96),
+                                     (4, 3, 3 * 1025, 96), (4, 3, 3 * 1024, 256), (4, 3, 3 * 1025, 256),
+                                     (5, 3, 3 * 300 - 1, 1021)])
 def test_encode_groups(lib, torch, dtype, n, k, q, r):
     P, A, _ = make_inputs(n, k, q, r, 1, 17, dtype, integer=True)
     code = lib.Code.systematic(P, 2)
