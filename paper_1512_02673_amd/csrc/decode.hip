@@ -24,6 +24,8 @@
 // E = 4 when a row's columns come in aligned groups of four or the rows lie
 // one after another, so that outputs go out as 16-byte stores; E = 1
 // otherwise, lanes on consecutive elements.
+#include <type_traits>
+
 #include "internal.h"
 #include "decode_common.h"
 
@@ -137,20 +139,24 @@ typedef double f64x4v __attribute__((ext_vector_type(4)));
 // of 65536 x 1: 716 and 220 us.)
 //
 // Combination: out[M] += D (16 rows a tile) * Y on v_mfma_f64_16x16x4f64, 32
-// elements per wave, the survivors' loads issued eight at a time and used for
+// elements per wave, the survivors' loads issued 32 (or all of 20) at a time and used for
 // all row tiles (one sweep over Y instead of one per eight missing blocks).
 // Every workgroup of a set repeats the elimination; RT row tiles hold any m
 // of the launch.  Neither RT nor the chunks change a result.
-constexpr int kWideThreads = 512;
-
-template <int RT, int E, typename YT>
-__global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a, DecodeSet single, int64_t chunks,
-                                                                   uint32_t elems_per_block, int LD) {
+//
+// Threads for COLS columns: systems of up to 64 columns take half, so that four
+// workgroups share a compute unit and one's elimination runs beside the others'
+// combinations.
+// One row tile of fp32 results: 78 registers, nothing spilled, and so three
+// workgroups a compute unit instead of two (600 (66,50) sets of 1000 x 1 25.6 us
+// against 30.5, 65536 x 4 240 against 278); fp64 results would spill 14.
+template <int RT, int E, int COLS, typename YT>
+__global__ __launch_bounds__(4 * COLS, RT == 1 && sizeof(YT) == 4 ? 6 : 1) void decode_wide_kernel(
+    DecodeArgs a, DecodeSet single, int64_t chunks, uint32_t elems_per_block, int LD) {
     __shared__ SetMeta sm;
     extern __shared__ __align__(16) double sA[];     // column c at sA[c * LD], LD odd, rows 0 .. m-1
-    constexpr int kThreads = kWideThreads, kWaves = kThreads / 64;
-    constexpr int kParts = kThreads / kMaxN, HR = 16 * RT / kParts;
-    static_assert(kThreads % kMaxN == 0 && 16 * RT % kParts == 0, "whole columns per part");
+    constexpr int kParts = 4, kThreads = kParts * COLS, kWaves = kThreads / 64, HR = 16 * RT / kParts;
+    static_assert(16 * RT % kParts == 0, "whole columns per part");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int k = a.k;
     const int64_t b = blockIdx.x / chunks;
@@ -163,8 +169,8 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a,
     if (m > 0) {
         // this thread's column, 0 .. m-1: G[S_par, M], then [-G[S_par, S_sys] | I],
         // and its rows part, part + kParts, ..
-        const int c = tid % kMaxN;
-        const int part = __builtin_amdgcn_readfirstlane(tid / kMaxN);
+        const int c = tid % COLS;
+        const int part = __builtin_amdgcn_readfirstlane(tid / COLS);
         const bool mine = c < m + k;
         double* mirror = sA + (mine ? c * LD : 0);
         double col[HR];
@@ -300,61 +306,143 @@ __global__ __launch_bounds__(kWideThreads) void decode_wide_kernel(DecodeArgs a,
 
     const int li = lane & 15, lk = lane >> 4;
     const int steps = (k + 3) / 4;
-    for (uint32_t base = e0 + 32 * wv; base < e1; base += 32 * kWaves) {
-        // past the chunk's end: its last element again (a column of the
-        // product depends on that column of Y only, and is not stored)
-        const uint32_t el[2] = {min(base + li, e1 - 1), min(base + 16 + li, e1 - 1)};
-        f64x4v acc[RT][2];
+    // E == 4: Y is the first operand and its lane li takes element 4 (li % 4) +
+    // li / 4 of a tile, so that lane (li, lk) gets elements 4 lk .. 4 lk + 3 of
+    // block M[16 rt + li] and stores them at once.
+    const int ye = E == 4 ? 4 * (li & 3) + (li >> 2) : li;
+    // A store instruction writes 64 bytes of each of 16 blocks: past the caches
+    // where these are whole 64-byte segments, else through them, which put the
+    // pieces of a segment together (600 (36,18) sets of 65536 x 4, fp64 results:
+    // 487 us past them, 259 through them; 20000 x 16, whole segments: 290 and 300).
+    const bool segments = (((reinterpret_cast<uintptr_t>(out) >> 2) | static_cast<uint64_t>(a.qb * a.ldo) |
+                            (s == 1 ? 0 : s | static_cast<uint64_t>(a.ldo))) & 15) == 0;
+    float* ob[E == 4 ? RT : 1];
+    uint32_t olim[E == 4 ? RT : 1];                  // the block's rows in A, 0 for no block
+    if constexpr (E == 4) {
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = f64x4v{0.0, 0.0, 0.0, 0.0};
-        for (int st = 0; st < steps; st += 8) {
-            YT yv[8][2];
+        for (int rt = 0; rt < RT; ++rt) {
+            const int bb = 16 * rt + li, w = sm.miss[bb < m ? bb : 0];
+            ob[rt] = out + sm.ooff[w];
+            olim[rt] = bb < m ? static_cast<uint32_t>(sm.lim[w]) : 0u;
+        }
+    }
+    // NB steps of four survivors' loads at a time
+    auto combine = [&](auto nb) __attribute__((always_inline)) {
+        constexpr int NB = decltype(nb)::value;
+        for (uint32_t base = e0 + 32 * wv; base < e1; base += 32 * kWaves) {
+            // past the chunk's end: its last element again (an element's products
+            // depend on that element of Y only, and are not stored)
+            const uint32_t last = e1 - 1, at0 = base + ye, at1 = at0 + 16;
+            const uint32_t el[2] = {at0 < last ? at0 : last, at1 < last ? at1 : last};
+            f64x4v acc[RT][2];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const YT* y = Y + sm.yoff[min(4 * (st + i) + lk, k - 1)];
-                yv[i][0] = y[el[0]];
-                yv[i][1] = y[el[1]];
-            }
+            for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = f64x4v{0.0, 0.0, 0.0, 0.0};
+            for (int st = 0; st < steps; st += NB) {
+                YT yv[NB][2];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int c = 4 * (st + i) + lk;
-                const bool ok = c < k;
-                const double y0 = ok ? static_cast<double>(yv[i][0]) : 0.0;
-                const double y1 = ok ? static_cast<double>(yv[i][1]) : 0.0;
-                const double* col = sA + (m + min(c, k - 1)) * LD;
+                for (int i = 0; i < NB; ++i) {
+                    const YT* y = Y + sm.yoff[min(4 * (st + i) + lk, k - 1)];
+                    yv[i][0] = y[el[0]];
+                    yv[i][1] = y[el[1]];
+                }
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    if (16 * rt < m && st + i < steps) {
-                        const int row = 16 * rt + li;
-                        const double d = col[min(row, m - 1)];
-                        const double dv = ok && row < m ? d : 0.0;
-                        acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y0, acc[rt][0], 0, 0, 0);
-                        acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y1, acc[rt][1], 0, 0, 0);
+                for (int i = 0; i < NB; ++i) {
+                    const int c = 4 * (st + i) + lk;
+                    const bool ok = c < k;
+                    const double y0 = ok ? static_cast<double>(yv[i][0]) : 0.0;
+                    const double y1 = ok ? static_cast<double>(yv[i][1]) : 0.0;
+                    const double* col = sA + (m + min(c, k - 1)) * LD;
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) {
+                        if (16 * rt < m && st + i < steps) {
+                            const int row = 16 * rt + li;
+                            const double d = col[min(row, m - 1)];
+                            const double dv = ok && row < m ? d : 0.0;
+                            if constexpr (E == 4) {
+                                acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(y0, dv, acc[rt][0], 0, 0, 0);
+                                acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(y1, dv, acc[rt][1], 0, 0, 0);
+                            } else {
+                                acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y0, acc[rt][0], 0, 0, 0);
+                                acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y1, acc[rt][1], 0, 0, 0);
+                            }
+                        }
                     }
                 }
             }
-        }
+            if constexpr (E == 4) {
+                uint32_t eh[2], th[2];
+                int64_t oh[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t e = base + 16 * h + li;
-            if (e < e1) {
-                const uint32_t t = e / s, col = e - t * s;
+                for (int h = 0; h < 2; ++h) {
+                    eh[h] = base + 16 * h + 4 * lk;
+                    th[h] = s == 1 ? eh[h] : eh[h] / s;           // s % 4 == 0: the four share a row
+                    oh[h] = static_cast<int64_t>(th[h]) * a.ldo + (s == 1 ? 0 : eh[h] - th[h] * s);
+                }
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) {
+                    if (a.c == nullptr) {
+                        f32x4v w[2];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int bb = 16 * rt + 4 * v + lk;
-                        if (bb < m) {
-                            const int w = sm.miss[bb];
-                            const double val = acc[rt][h][v];
-                            if (t < static_cast<uint32_t>(sm.lim[w]))
-                                store_out<1>(a, out, sm.ooff[w] + static_cast<int64_t>(t) * a.ldo + col, &val);
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) w[h][i] = static_cast<float>(acc[rt][h][i]);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            if (eh[h] >= e1 || th[h] >= olim[rt]) continue;
+                            const uint32_t left = s == 1 ? (e1 < olim[rt] ? e1 : olim[rt]) - eh[h] : 4u;
+                            float* o = ob[rt] + oh[h];
+                            if (left < 4) {
+                                for (uint32_t i = 0; i < left; ++i) o[i] = w[h][i];
+                            } else if (segments) {
+                                __builtin_nontemporal_store(w[h], reinterpret_cast<f32x4v_any*>(o));
+                            } else {      // between fences, or the compiler makes one plain store of the two
+                                asm volatile("" ::: "memory");
+                                *reinterpret_cast<f32x4v_any*>(o) = w[h];
+                                asm volatile("" ::: "memory");
+                            }
+                        }
+                    } else {
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            if (eh[h] >= e1 || th[h] >= olim[rt]) continue;
+                            const double v4[4] = {acc[rt][h][0], acc[rt][h][1], acc[rt][h][2], acc[rt][h][3]};
+                            const uint32_t left = s == 1 ? (e1 < olim[rt] ? e1 : olim[rt]) - eh[h] : 4u;
+                            if (left >= 4) {
+                                store_out<4>(a, ob[rt], oh[h], v4);
+                            } else {
+                                for (uint32_t i = 0; i < left; ++i) store_out<1>(a, ob[rt], oh[h] + i, &v4[i]);
+                            }
+                        }
+                    }
+                }
+                continue;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t e = base + 16 * h + li;
+                if (e < e1) {
+                    const uint32_t t = e / s, col = e - t * s;
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int bb = 16 * rt + 4 * v + lk;
+                            if (bb < m) {
+                                const int w = sm.miss[bb];
+                                const double val = acc[rt][h][v];
+                                if (t < static_cast<uint32_t>(sm.lim[w]))
+                                    store_out<1>(a, out, sm.ooff[w] + static_cast<int64_t>(t) * a.ldo + col, &val);
+                            }
                         }
                     }
                 }
             }
         }
+    };
+    if constexpr (COLS == 64) {
+        if (steps <= 5) return combine(std::integral_constant<int, 5>{});
     }
+    combine(std::integral_constant<int, 8>{});
 }
 
 // ---------------------------------------------------------------- fast path
@@ -855,24 +943,35 @@ hipError_t launch_fast(const DecodeArgs& a, const DecodeSet& single, hipStream_t
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) % 16) == 0; }
 
-template <int RT, int E>
-hipError_t launch_wide(const DecodeArgs& a, const DecodeSet& single, int mmax, hipStream_t st) {
-    // About 512 workgroups of at least 64 elements: each repeats the
-    // elimination, which outweighs the rest of a short chunk.
+template <int RT, int E, int COLS>
+hipError_t launch_wide_cols(const DecodeArgs& a, const DecodeSet& single, int mmax, hipStream_t st) {
+    // Whole rounds of the workgroups that run at once: two a compute unit, four
+    // of the small ones, one with the registers of four row tiles.  (600 sets
+    // in one 512-thread workgroup each ran two rounds, the second with 88.)
+    constexpr int kThreads = 4 * COLS;
     const int64_t total = a.qb * a.s;
-    const Chunks cut = split_chunks(total, ceil_div(512, a.batch), 32);
+    const Chunks cut = split_chunks(total, chunks_per_set(total, a.batch, RT == 4 ? 256 : 256 * 1024 / kThreads), 32);
     const int64_t blocks = cut.count * a.batch;
-    if (!grid_fits(blocks, kWideThreads)) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, kThreads)) return hipErrorInvalidConfiguration;
     const int LD = std::max(mmax, 1) | 1;            // odd: columns start in different banks
     const size_t shmem = static_cast<size_t>(a.k + mmax) * LD * sizeof(double);
     const dim3 grid(static_cast<unsigned>(blocks));
     if (a.y_f64)
-        hipLaunchKernelGGL((decode_wide_kernel<RT, E, double>), grid, dim3(kWideThreads), shmem, st, a, single, cut.count,
+        hipLaunchKernelGGL((decode_wide_kernel<RT, E, COLS, double>), grid, dim3(kThreads), shmem, st, a, single, cut.count,
                            static_cast<uint32_t>(cut.per), LD);
     else
-        hipLaunchKernelGGL((decode_wide_kernel<RT, E, float>), grid, dim3(kWideThreads), shmem, st, a, single, cut.count,
+        hipLaunchKernelGGL((decode_wide_kernel<RT, E, COLS, float>), grid, dim3(kThreads), shmem, st, a, single, cut.count,
                            static_cast<uint32_t>(cut.per), LD);
     return hipGetLastError();
+}
+
+// By the code, as the arithmetic does not depend on it but a set's chunks do.
+template <int RT, int E>
+hipError_t launch_wide(const DecodeArgs& a, const DecodeSet& single, int mmax, hipStream_t st) {
+    if constexpr (RT == 2) {
+        if (a.k + std::min(a.k, a.n - a.k) <= 64) return launch_wide_cols<RT, E, 64>(a, single, mmax, st);
+    }
+    return launch_wide_cols<RT, E, kMaxN>(a, single, mmax, st);
 }
 
 }  // namespace

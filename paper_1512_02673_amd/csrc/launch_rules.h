@@ -17,6 +17,23 @@ constexpr Chunks split_chunks(int64_t total, int64_t want, int64_t unit) {
     return {per, (n + per - 1) / per};
 }
 
+// Chunks per survivor set where `resident` workgroups run at once and each
+// repeats its set's elimination, worth about 384 elements of the work: the count
+// that fills some number of rounds of them at the least cost.
+constexpr int64_t chunks_per_set(int64_t total, int64_t sets, int64_t resident) {
+    const int64_t least = (sets + resident - 1) / resident;
+    int64_t best = 1, best_cost = -1;
+    for (int64_t rounds = least; rounds < least + 8; ++rounds) {
+        const int64_t c = rounds * resident / sets > 1 ? rounds * resident / sets : 1;
+        const int64_t cost = rounds * (384 + (total + c - 1) / c);
+        if (best_cost < 0 || cost < best_cost) {
+            best = c;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 // End of the chunk that starts at e0 < total (e0 + per may pass 2^31).
 constexpr uint32_t chunk_end(uint32_t e0, uint32_t per, uint32_t total) {
     return e0 + (per < total - e0 ? per : total - e0);

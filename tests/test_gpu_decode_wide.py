@@ -52,7 +52,9 @@ def _results(P, k, q, s, seed):
 # second half of the rows, the widest accepted system, more than 64 survivors,
 # codes without parity workers (k = 128 takes the whole survivor mask)
 CODES = [(128, 128, 0), (65, 65, 0), (127, 127, 0), (128, 127, 1), (66, 50, 16), (66, 50, 0), (34, 17, 17),
-         (96, 64, 31), (128, 96, 32), (66, 33, 33), (100, 50, 48), (128, 74, 54)]
+         (96, 64, 31), (128, 96, 32), (66, 33, 33), (100, 50, 48), (128, 74, 54),
+         # systems of up to 64 columns (half the threads), up to 20 survivors, and exactly 64 columns
+         (36, 18, 9), (100, 20, 20), (100, 20, 3), (60, 40, 20), (110, 32, 32)]
 
 
 @pytest.mark.parametrize("n,k,m", CODES)

@@ -74,11 +74,18 @@ int main() {
         CHECK(coded::grid_fits(most, threads) && most * threads < (1ll << 32), "%d threads\n", threads);
         CHECK(!coded::grid_fits(most + 1, threads) && !coded::grid_fits(1ll << 62, threads), "%d threads\n", threads);
     }
-    for (int64_t batch : {coded::kSetsPerLaunch, coded::kSetsPerLaunch - 1, int64_t(1000), int64_t(1)})
-        for (int64_t total : {int64_t(1), int64_t(1000), (int64_t(1) << 31) - 1}) {
-            const auto c = coded::split_chunks(total, (1024 + batch - 1) / batch, 16);
-            CHECK(coded::grid_fits(c.count * batch, 512), "%lld sets of %lld\n", static_cast<long long>(batch), static_cast<long long>(total));
-        }
+    for (int64_t batch : {coded::kSetsPerLaunch, coded::kSetsPerLaunch - 1, int64_t(1000), int64_t(600), int64_t(1)})
+        for (int64_t total : {int64_t(1), int64_t(1000), (int64_t(1) << 31) - 1})
+            for (int64_t resident : {int64_t(256), int64_t(512)}) {
+                const auto c = coded::split_chunks(total, (1024 + batch - 1) / batch, 16);
+                CHECK(coded::grid_fits(c.count * batch, 512), "%lld sets of %lld\n", static_cast<long long>(batch), static_cast<long long>(total));
+                const int64_t per_set = coded::chunks_per_set(total, batch, resident);
+                const auto w = coded::split_chunks(total, per_set, 32);
+                CHECK(per_set >= 1 && coded::grid_fits(w.count * batch, 512), "%lld wide sets of %lld\n", static_cast<long long>(batch), static_cast<long long>(total));
+                // no round is left nearly empty while a set could be cut
+                const int64_t blocks = per_set * batch, rounds = (blocks + resident - 1) / resident;
+                CHECK(batch != 600 || total < 10000 || blocks * 10 >= rounds * resident * 9, "600 sets of %lld: %lld workgroups\n", static_cast<long long>(total), static_cast<long long>(blocks));
+            }
 }
 """)
 
