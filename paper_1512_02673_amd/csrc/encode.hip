@@ -281,7 +281,7 @@ hipError_t launch_encode_f32(const EncodeArgs& a, hipStream_t st) {
     const bool vec = a.r >= 4 && a.qb * a.r * groups > kSingleF32;
     const int V = vec ? 4 : 1;
     const int64_t chunks = ceil_div(a.r, static_cast<int64_t>(kThreads) * V);
-    if (chunks * groups > 65535) return hipErrorInvalidConfiguration;
+    if (chunks > 65535) return hipErrorInvalidConfiguration;
     const int width = row_threads(a.r, V);
     const int64_t rows = ceil_div(a.qb, kThreads / width);
     const int64_t blocks = groups > 1 ? ceil_div(rows, 8) * 8 * groups : rows;
@@ -301,7 +301,7 @@ hipError_t launch_encode_bf16(const EncodeArgs& a, hipStream_t st) {
     const bool vec = a.r >= 8 && a.qb * a.r * groups > kSingleBf16;
     const int V = vec ? 8 : 1;
     const int64_t chunks = ceil_div(a.r, static_cast<int64_t>(kThreads) * V);
-    if (chunks * groups > 65535) return hipErrorInvalidConfiguration;
+    if (chunks > 65535) return hipErrorInvalidConfiguration;
     const int width = row_threads(a.r, V);
     const int64_t rows = ceil_div(a.qb, kThreads / width);
     const int64_t blocks = groups > 1 ? ceil_div(rows, 8) * 8 * groups : rows;

@@ -45,3 +45,17 @@ def test_encode_groups(lib, torch, dtype, n, k, q, r):
         assert np.array_equal(got[0], ref) and np.all(got[1] == 0)
     else:
         assert np.array_equal(got[0] + got[1], ref)     # whole numbers below 2^16: 8 + 8 bits hold them
+
+
+def test_groups_of_the_longest_rows(lib, torch):
+    # 16 groups of parity rows, 4102 column chunks each: more than 65535 together, which a launch takes
+    n, r = 128, 4_200_000
+    P = np.arange(1, n, dtype=np.float32).reshape(n - 1, 1)
+    code = lib.Code.systematic(P, 1)
+    A = (torch.arange(r, device="cuda", dtype=torch.int64) % 1021 - 510).to(torch.float32).reshape(1, r)
+    par = lib.alloc_parity(code, 1, r, A.dtype)
+    lib.coded_encode(code, A, par)
+    torch.cuda.synchronize()
+    got = par.reshape(n - 1, r)
+    for p in range(n - 1):
+        assert bool((got[p] == A[0] * float(p + 1)).all())      # whole numbers below 2^24
