@@ -189,28 +189,11 @@ __global__ __launch_bounds__(kThreads) void shuffle_decode_kernel(const float* _
             continue;
         }
         const typename R::T mv = R::load(M + m * ldm + c);
-        if (cnt <= kTermRegs) {
-            typename R::T x[kTermRegs];
-#pragma unroll
-            for (int j = 0; j < kTermRegs; ++j)
-                if (j < cnt) x[j] = R::load(A + static_cast<int64_t>(rows[b + j]) * lda + c);
-#pragma unroll
-            for (int i = 0; i < kTermRegs; ++i) {
-                if (i < cnt) {
-                    typename R::T acc = mv;
-#pragma unroll
-                    for (int j = 0; j < kTermRegs; ++j)
-                        if (j < cnt && j != i) acc = acc - x[j];
-                    R::store(out + (b + i) * ldo + c, acc);
-                }
-            }
-        } else {
-            for (int64_t d = b; d < e; ++d) {
-                typename R::T acc = mv;
-                for (int64_t t = b; t < e; ++t)
-                    if (t != d) acc = acc - R::load(A + static_cast<int64_t>(rows[t]) * lda + c);
-                R::store(out + d * ldo + c, acc);
-            }
+        for (int64_t d = b; d < e; ++d) {
+            typename R::T acc = mv;
+            for (int64_t t = b; t < e; ++t)
+                if (t != d) acc = acc - R::load(A + static_cast<int64_t>(rows[t]) * lda + c);
+            R::store(out + d * ldo + c, acc);
         }
     }
 }
