@@ -154,11 +154,15 @@ def _torch():
 
 def _stream(stream=None):
     """The HIP stream handle of `stream`, or of the current device's current stream, read
-    without making a Stream object (3 us of a small call's 12)."""
+    without making a Stream object (3 us of a small call's 12) where torch has the call for it,
+    which is not part of its public interface."""
     if stream is not None:
         return stream.cuda_stream
     torch = _torch()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 _DTYPE_CODES: dict = {}   # filled on first use: torch is imported late
