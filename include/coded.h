@@ -186,8 +186,9 @@ coded_status coded_worker_mm(const coded_code* code, coded_dtype dt, const void*
  * rows feed the products from on-chip memory); other inputs run the two steps
  * one after the other.  Products of one worker may be summed in another order
  * than coded_worker_mm's (fp32 accumulation; equal within rounding).
- *   A, X, s, ldx, Y, y_dt, workspace as for coded_worker_mm (workspace is
- *   required for bf16 inputs); parity as for coded_encode.
+ *   A, X, s, ldx, Y, y_dt as for coded_worker_mm; parity as for coded_encode.
+ *   workspace  device, coded_sizes' worker_workspace_bytes: X transposed for
+ *              the one read of A (required for bf16 inputs of any shape).
  */
 coded_status coded_encode_worker_mm(const coded_code* code, coded_dtype dt, const void* A, int64_t q, int64_t r,
                                     int64_t lda, void* parity, const void* X, int64_t s, int64_t ldx, void* Y,
@@ -319,7 +320,8 @@ coded_status coded_matmul_noalloc(const coded_code* code, coded_dtype dt, const 
  *   dt, A, parity, X, s, ldx   as coded_worker_mm; parity must be ready.
  *   Y          device n x qb x s of y_dt (as coded_worker_mm); rows of
  *              workers that do not run are left untouched.
- *   workspace  coded_sizes' worker_workspace_bytes (BF16: required).
+ *   workspace  not read: the products take X as it is.  BF16 calls are still
+ *              refused without one (any device pointer will do).
  *   out, ldo, info   as coded_decode.
  *   survivors_out  host int32[k] or NULL: the survivors in arrival order.
  *   timeline_out   host double[3 n] or NULL: for worker i, [3i] its start

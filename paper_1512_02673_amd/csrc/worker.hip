@@ -375,9 +375,9 @@ __global__ __launch_bounds__(256) void gemv_short_kernel(WorkerArgs a) {
 }
 
 // General shapes (any r, s, strides): one block row per wave (all planes of a
-// parity row), scalar loads, columns of X in groups of SC.  Used for inputs
-// the vector GEMV and the matrix-core kernel cannot take (r or lda not a
-// multiple of 4, or unaligned pointers).
+// parity row), scalar loads, columns of X in groups of SC.  Used with several
+// columns for what the matrix-core kernel does not take: rows of fewer than four
+// elements or more than 2^30, and a bfloat16 lo plane.
 template <int SC>
 __global__ __launch_bounds__(kThreads) void gemm_small_f32_kernel(WorkerArgs a) {
     int worker;

@@ -440,7 +440,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_mfma_kernel(WorkerArgs a, 
     }
 }
 
-// Short rows (up to 256 elements, whole 16-byte pieces): one step of K, so a
+// Short rows (up to 384 elements, whole 16-byte pieces): one step of K, so a
 // workgroup of the kernel above would stage X for every 64 or 128 rows and wait
 // for its few loads with nothing to overlap them.  Here eight waves take two
 // tiles of 16 row slots each (of a two-plane parity row: its hi and its lo

@@ -153,7 +153,7 @@ def test_worker_products_gaussian(lib, torch, n, k, q, r, s, planes):
                                        (5, 3, 31, 64, 7), (8, 5, 90, 128, 100), (4, 2, 10, 8, 1), (5, 3, 20, 12, 3)])
 @pytest.mark.parametrize("planes", [1, 2])
 def test_worker_products_bf16_integer_bit_exact(lib, torch, n, k, q, r, s, planes):
-    """bf16 blocks and X on the matrix cores (and the vector kernel without a workspace):
+    """bf16 blocks and X on the matrix cores, with a workspace and without (the products read none):
     integer-valued inputs make every fp32 sum exact, so Y must equal the oracle's exactly."""
     P, A, X = make_inputs(n, k, q, r, s, 19, "bf16", integer=True)
     code = lib.Code.systematic(P, planes)

@@ -81,6 +81,19 @@ def test_strides_and_alignment(lib, torch, apad, xpad, lead, r, s):
     _check(lib, torch, 5, 3, 70, r, s, 2, apad, xpad, lead)
 
 
+# Rows shorter than one 16-byte piece: the vector kernel.
+@pytest.mark.parametrize("r", [2, 3, 5, 6, 7])
+@pytest.mark.parametrize("s,planes,apad,xpad", [(1, 2, 0, 0), (1, 1, 3, 0), (4, 2, 1, 2), (5, 1, 0, 3), (18, 2, 2, 1)])
+def test_tiny_rows(lib, torch, r, s, planes, apad, xpad):
+    _check(lib, torch, 6, 4, 101, r, s, planes, apad=apad, xpad=xpad, lead=1)
+
+
+def test_tiny_rows_mask(lib, torch):
+    mask = np.zeros(6, dtype=np.uint8)
+    mask[[1, 4]] = 1
+    _check(lib, torch, 6, 4, 101, 6, 3, 2, mask=mask)
+
+
 # Rows of whole 16-byte pieces that take one step of K (up to 224 elements; 256
 # with up to 32 columns, 384 with up to 16), either side of the steps of 64, one
 # and two column tiles traded between rows, column remainders of 1 to 3, blocks
