@@ -33,7 +33,7 @@ METRIC = "coded A·X decoded products/sec + achieved HBM GB/s (GEMV) / MFMA % (G
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "worker_gemv_traffic_gemv16x12.json")
 KERNEL_SOURCES = ["paper_1512_02673_amd/csrc/worker.hip", "paper_1512_02673_amd/csrc/worker_common.h",
-                  "paper_1512_02673_amd/csrc/internal.h"]
+                  "paper_1512_02673_amd/csrc/internal.h", "paper_1512_02673_amd/csrc/launch_rules.h"]
 
 
 # Runtime-model kernel: executed VALU instructions per launch from a committed
@@ -288,7 +288,7 @@ def gemv_workload(args):
     algo_bytes = 4.0 * q * r + par_elem * (n - k) * qb * r + 4.0 * r + 8.0 * n * qb
     gemv_mean_ms = float(gemv_ms.mean())
     achieved = algo_bytes / (gemv_mean_ms * 1e-3) / 1e9
-    kname = f"gemv_wg_kernel<4, 8, 256, {'true' if lo16 else 'false'}>"
+    kname = f"gemv_wg_kernel<4, 8, 256, {'true' if lo16 else 'false'}, true, false>"
     if w.name == "gemv16x12_65536x8192":
         traffic = measured_traffic(algo_bytes)
     else:
@@ -536,15 +536,15 @@ def decode_workload(args):
                             f"uniform random sets with exactly {args.exact_parity} parity survivors (repeats allowed)")},
         "roofline": {"bound": "hbm", "kernel": "decode_mfma_kernel", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": algo_bytes,
-                     "traffic": measured_kernel_traffic(w.name, "decode_mfma_kernel<12, 4, double, true, true>", algo_bytes), "fp64_tflops": flops / mean_s / 1e12, "fp64_frac": flops / mean_s / 78.6e12,
-                     "mfma_counters": measured_mfma(w.name, "decode_mfma_kernel<12, 4, double, true, true>")},
-        "products": {"kernel": "gemm_f32_mfma_kernel<1, 2, true, 128, 2, true> (64 worker products, s = 8, once per run)",
+                     "traffic": measured_kernel_traffic(w.name, "decode_mfma_kernel<12, 4, double, true, true, false>", algo_bytes), "fp64_tflops": flops / mean_s / 1e12, "fp64_frac": flops / mean_s / 78.6e12,
+                     "mfma_counters": measured_mfma(w.name, "decode_mfma_kernel<12, 4, double, true, true, false>")},
+        "products": {"kernel": "gemm_f32_mfma_kernel<1, 2, true, 128, 2, true, false> (64 worker products, s = 8, once per run)",
                      "ms_mean": float(prod_ms.mean()), "ms_min": float(prod_ms.min()),
                      "algorithmic_bytes_per_launch": prod_bytes,
                      "achieved_gbs": prod_bytes / (float(prod_ms.mean()) * 1e-3) / 1e9,
                      "hbm_frac": prod_bytes / (float(prod_ms.mean()) * 1e-3) / 1e9 / HBM_PEAK_GBS,
                      "fp64_tflops": prod_flops / (float(prod_ms.mean()) * 1e-3) / 1e12,
-                     "traffic": measured_kernel_traffic(w.name, "gemm_f32_mfma_kernel<1, 2, true, 128, 2, true>", prod_bytes)},
+                     "traffic": measured_kernel_traffic(w.name, "gemm_f32_mfma_kernel<1, 2, true, 128, 2, true, false>", prod_bytes)},
     }
     if not args.no_cpu_baseline:
         result["cpu_baseline"] = cpu_baseline_decode(w, A, X, P, sets, out, args.cpu_decodes)
@@ -649,8 +649,8 @@ def gd_workload(args):
         "roofline": {"bound": "hbm", "kernel": "gemv_wg_kernel (A and A^T launches)", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "algorithmic_bytes_per_launch": [bA, bT],
-                     "traffic": [measured_kernel_traffic(w.name, "gemv_wg_kernel<4, 4, 256, false>", bA),
-                                 measured_kernel_traffic(w.name, "gemv_wg_kernel<4, 8, 256, false>", bT)],
+                     "traffic": [measured_kernel_traffic(w.name, "gemv_wg_kernel<4, 4, 256, false, true, false>", bA),
+                                 measured_kernel_traffic(w.name, "gemv_wg_kernel<4, 8, 256, false, true, false>", bT)],
                      "step_frac": (bA + bT) / (step_ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
     }
     return result
@@ -826,8 +826,8 @@ def runtime_sim_workload(args):
         "config": {"workload": "runtime_sim_10x5", "n": n, "k": k, "shift": 1.0, "rate": 1.0,
                    "draws_per_step": draws, "schemes": ["uncoded", "repetition", "mds"]},
         "means_last_step": dict(zip(["uncoded", "repetition", "mds"], means)),
-        "roofline": {"bound": "alu", "kernel": "runtime_sim_kernel<12>",
-                     "note": "vector-issue bound: 64-bit SplitMix64 words and the O(n^2) ranking per draw; "
+        "roofline": {"bound": "alu", "kernel": "runtime_sim_kernel<10, 9>",
+                     "note": "vector-issue bound: 64-bit SplitMix64 words and a sorting network per draw; "
                              "achieved = executed VALU wave-instructions per launch (SQ_INSTS_VALU) / launch time",
                      "achieved": achieved, "peak": ALU_PEAK_G, "unit": "G wave-instructions/s",
                      "frac": achieved / ALU_PEAK_G if achieved is not None else None,
