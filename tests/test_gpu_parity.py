@@ -153,7 +153,7 @@ def test_worker_products_gaussian(lib, torch, n, k, q, r, s, planes):
                                        (5, 3, 31, 64, 7), (8, 5, 90, 128, 100), (4, 2, 10, 8, 1), (5, 3, 20, 12, 3)])
 @pytest.mark.parametrize("planes", [1, 2])
 def test_worker_products_bf16_integer_bit_exact(lib, torch, n, k, q, r, s, planes):
-    """bf16 blocks and X on the matrix cores, with a workspace and without (the products read none):
+    """bf16 blocks and X on the matrix cores, without a workspace and with one, which stays unread:
     integer-valued inputs make every fp32 sum exact, so Y must equal the oracle's exactly."""
     P, A, X = make_inputs(n, k, q, r, s, 19, "bf16", integer=True)
     code = lib.Code.systematic(P, planes)
@@ -161,7 +161,9 @@ def test_worker_products_bf16_integer_bit_exact(lib, torch, n, k, q, r, s, plane
     par = lib.alloc_parity(code, q, r, torch.bfloat16)
     lib.coded_encode(code, dA, par)
     ref = oc.worker_products(oc.encode(oc.systematic_generator(P), oc.pad_and_split(A, k)), X)
-    for ws in ("auto", None):
+    for ws in ("auto", None, lib.worker_workspace(code, dA, dX)):
+        if torch.is_tensor(ws):
+            ws.fill_(255)
         Y = lib.alloc_y(code, q, s, torch.float32)
         Y.fill_(float("nan"))
         lib.coded_worker_mm(code, dA, par, dX, Y, workspace=ws)
