@@ -326,44 +326,83 @@ __global__ __launch_bounds__(4 * COLS, RT == 1 && sizeof(YT) == 4 ? 6 : 1) void 
             olim[rt] = bb < m ? static_cast<uint32_t>(sm.lim[w]) : 0u;
         }
     }
-    // NB steps of four survivors' loads at a time
-    auto combine = [&](auto nb) __attribute__((always_inline)) {
-        constexpr int NB = decltype(nb)::value;
+    // NB steps of four survivors' loads at a time, R row tiles.  HELD (steps ==
+    // NB): D and the survivors' addresses stay in registers; the vector
+    // instructions that fetch them for every tile run beside no matrix instruction
+    // of their SIMD (600 (36,18) sets, fp64 results, 16384 x 8 141 us without, 116
+    // so; 20000 x 16 313 and 255; (100,20), 3000 x 64 232 and 201).
+    auto combine = [&](auto nb, auto tiles, auto held) __attribute__((always_inline)) {
+        constexpr int NB = decltype(nb)::value, R = decltype(tiles)::value;
+        constexpr bool HELD = decltype(held)::value;
+        const YT* yp[HELD ? NB : 1];
+        double dh[HELD ? NB : 1][R];
+        if constexpr (HELD) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int c = 4 * i + lk, at = min(c, k - 1);
+                yp[i] = Y + sm.yoff[at];
+#pragma unroll
+                for (int rt = 0; rt < R; ++rt) {
+                    const int row = 16 * rt + li;
+                    const double d = sA[(m + at) * LD + min(row, m - 1)];
+                    dh[i][rt] = c < k && row < m ? d : 0.0;
+                }
+            }
+        }
         for (uint32_t base = e0 + 32 * wv; base < e1; base += 32 * kWaves) {
             // past the chunk's end: its last element again (an element's products
             // depend on that element of Y only, and are not stored)
             const uint32_t last = e1 - 1, at0 = base + ye, at1 = at0 + 16;
             const uint32_t el[2] = {at0 < last ? at0 : last, at1 < last ? at1 : last};
-            f64x4v acc[RT][2];
+            f64x4v acc[R][2];
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) acc[rt][0] = acc[rt][1] = f64x4v{0.0, 0.0, 0.0, 0.0};
-            for (int st = 0; st < steps; st += NB) {
+            for (int rt = 0; rt < R; ++rt) acc[rt][0] = acc[rt][1] = f64x4v{0.0, 0.0, 0.0, 0.0};
+            auto multiply = [&](int rt, double dv, double y0, double y1) __attribute__((always_inline)) {
+                if constexpr (E == 4) {
+                    acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(y0, dv, acc[rt][0], 0, 0, 0);
+                    acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(y1, dv, acc[rt][1], 0, 0, 0);
+                } else {
+                    acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y0, acc[rt][0], 0, 0, 0);
+                    acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y1, acc[rt][1], 0, 0, 0);
+                }
+            };
+            if constexpr (HELD) {
                 YT yv[NB][2];
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
-                    const YT* y = Y + sm.yoff[min(4 * (st + i) + lk, k - 1)];
-                    yv[i][0] = y[el[0]];
-                    yv[i][1] = y[el[1]];
+                    yv[i][0] = yp[i][el[0]];
+                    yv[i][1] = yp[i][el[1]];
                 }
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
-                    const int c = 4 * (st + i) + lk;
-                    const bool ok = c < k;
+                    const bool ok = i < NB - 1 || 4 * i + lk < k;
                     const double y0 = ok ? static_cast<double>(yv[i][0]) : 0.0;
                     const double y1 = ok ? static_cast<double>(yv[i][1]) : 0.0;
-                    const double* col = sA + (m + min(c, k - 1)) * LD;
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
-                        if (16 * rt < m && st + i < steps) {
-                            const int row = 16 * rt + li;
-                            const double d = col[min(row, m - 1)];
-                            const double dv = ok && row < m ? d : 0.0;
-                            if constexpr (E == 4) {
-                                acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(y0, dv, acc[rt][0], 0, 0, 0);
-                                acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(y1, dv, acc[rt][1], 0, 0, 0);
-                            } else {
-                                acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y0, acc[rt][0], 0, 0, 0);
-                                acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(dv, y1, acc[rt][1], 0, 0, 0);
+                    for (int rt = 0; rt < R; ++rt) multiply(rt, dh[i][rt], y0, y1);
+                }
+            } else {
+                for (int st = 0; st < steps; st += NB) {
+                    YT yv[NB][2];
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        const YT* y = Y + sm.yoff[min(4 * (st + i) + lk, k - 1)];
+                        yv[i][0] = y[el[0]];
+                        yv[i][1] = y[el[1]];
+                    }
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        const int c = 4 * (st + i) + lk;
+                        const bool ok = c < k;
+                        const double y0 = ok ? static_cast<double>(yv[i][0]) : 0.0;
+                        const double y1 = ok ? static_cast<double>(yv[i][1]) : 0.0;
+                        const double* col = sA + (m + min(c, k - 1)) * LD;
+#pragma unroll
+                        for (int rt = 0; rt < R; ++rt) {
+                            if (16 * rt < m && st + i < steps) {
+                                const int row = 16 * rt + li;
+                                const double d = col[min(row, m - 1)];
+                                multiply(rt, ok && row < m ? d : 0.0, y0, y1);
                             }
                         }
                     }
@@ -379,7 +418,7 @@ __global__ __launch_bounds__(4 * COLS, RT == 1 && sizeof(YT) == 4 ? 6 : 1) void 
                     oh[h] = static_cast<int64_t>(th[h]) * a.ldo + (s == 1 ? 0 : eh[h] - th[h] * s);
                 }
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
+                for (int rt = 0; rt < R; ++rt) {
                     if (a.c == nullptr) {
                         f32x4v w[2];
 #pragma unroll
@@ -423,7 +462,7 @@ __global__ __launch_bounds__(4 * COLS, RT == 1 && sizeof(YT) == 4 ? 6 : 1) void 
                 if (e < e1) {
                     const uint32_t t = e / s, col = e - t * s;
 #pragma unroll
-                    for (int rt = 0; rt < RT; ++rt) {
+                    for (int rt = 0; rt < R; ++rt) {
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const int bb = 16 * rt + 4 * v + lk;
@@ -439,10 +478,14 @@ __global__ __launch_bounds__(4 * COLS, RT == 1 && sizeof(YT) == 4 ? 6 : 1) void 
             }
         }
     };
+    constexpr std::integral_constant<int, 5> five{};
+    constexpr std::integral_constant<int, 8> eight{};
+    constexpr std::integral_constant<int, RT> all{};
     if constexpr (COLS == 64) {
-        if (steps <= 5) return combine(std::integral_constant<int, 5>{});
+        if (steps == 5 && m <= 16) return combine(five, std::integral_constant<int, 1>{}, std::true_type{});
+        if (steps == 5) return combine(five, all, std::true_type{});
     }
-    combine(std::integral_constant<int, 8>{});
+    combine(eight, all, std::false_type{});
 }
 
 // ---------------------------------------------------------------- fast path
